@@ -205,117 +205,6 @@ __global__ void adjoint_weights_kernel(const void* W, void* Wt, int cin, int cou
     }
 }
 
-// gW partials: grid (nblk, 9 paths); each workgroup reduces its sites for every (b, a).
-template <int R, int COUT>
-__global__ void __launch_bounds__(256) ptconv_wgrad_kernel(PTArgs A, const float2* __restrict__ gout, int nsamples,
-                                                           double* __restrict__ partials)
-{
-    const int p = blockIdx.y;
-    const uint32_t Vh = (uint32_t)A.g.Vh;
-    const long long nsites = 2ll * Vh * nsamples;
-    __shared__ double lds[2 * COUT][4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int b = 0; b < A.cin; ++b) {
-        double acc[2 * COUT];
-#pragma unroll
-        for (int i = 0; i < 2 * COUT; ++i) acc[i] = 0.0;
-        for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < nsites; k += (long long)gridDim.x * 256) {
-            const int n = (int)(k / (2 * Vh));
-            const uint32_t idx = (uint32_t)(k - (long long)n * 2 * Vh);
-            const int par = idx >= Vh ? 1 : 0;
-            const uint32_t cb = idx - (uint32_t)par * Vh;
-            const float2* in = A.in + (size_t)n * A.in_sample;
-            const float2* go = gout + (size_t)n * A.out_sample;
-            float t[6];
-            if (p == 0) {
-#pragma unroll
-                for (int kk = 0; kk < 3; ++kk) {
-                    const float2 q = in[fidx(b, par, kk, Vh, cb)];
-                    t[2 * kk] = q.x;
-                    t[2 * kk + 1] = q.y;
-                }
-            } else {
-                int c[4];
-                cb_coords(A.g, cb, par, c);
-                const int mu = (p - 1) & 3;
-                const bool fwd = p <= 4;
-                uint32_t nb;
-                bool edge;
-                switch (mu * 2 + (fwd ? 0 : 1)) {
-                case 0: nb = neighbour<0, true>(A.g, cb, c); edge = on_boundary<0, true>(A.g, c); break;
-                case 1: nb = neighbour<0, false>(A.g, cb, c); edge = on_boundary<0, false>(A.g, c); break;
-                case 2: nb = neighbour<1, true>(A.g, cb, c); edge = on_boundary<1, true>(A.g, c); break;
-                case 3: nb = neighbour<1, false>(A.g, cb, c); edge = on_boundary<1, false>(A.g, c); break;
-                case 4: nb = neighbour<2, true>(A.g, cb, c); edge = on_boundary<2, true>(A.g, c); break;
-                case 5: nb = neighbour<2, false>(A.g, cb, c); edge = on_boundary<2, false>(A.g, c); break;
-                case 6: nb = neighbour<3, true>(A.g, cb, c); edge = on_boundary<3, true>(A.g, c); break;
-                default: nb = neighbour<3, false>(A.g, cb, c); edge = on_boundary<3, false>(A.g, c); break;
-                }
-                const int lpar = fwd ? par : 1 - par;
-                const uint32_t lcb = fwd ? cb : nb;
-                float u[18], v[6];
-                LinkIO<P_F32, R, false>::load(A.gauge + (size_t)(2 * mu + lpar) * link_site_bytes(P_F32, R) * A.g.ps, A.g.ps, lcb, u);
-#pragma unroll
-                for (int kk = 0; kk < 3; ++kk) {
-                    const float2 q = in[fidx(b, 1 - par, kk, Vh, nb)];
-                    v[2 * kk] = q.x;
-                    v[2 * kk + 1] = q.y;
-                }
-                mat_vec(u, v, t, !fwd);
-                const float s = edge ? A.g.bcf[mu] : 1.0f;
-#pragma unroll
-                for (int i = 0; i < 6; ++i) t[i] *= s;
-            }
-#pragma unroll
-            for (int a = 0; a < COUT; ++a) {
-                float re = 0.f, im = 0.f;
-#pragma unroll
-                for (int kk = 0; kk < 3; ++kk) {
-                    const float2 gq = go[fidx(a, par, kk, Vh, cb)];
-                    // g * conj(t)
-                    re += gq.x * t[2 * kk] + gq.y * t[2 * kk + 1];
-                    im += gq.y * t[2 * kk] - gq.x * t[2 * kk + 1];
-                }
-                acc[2 * a] += re;
-                acc[2 * a + 1] += im;
-            }
-        }
-        // workgroup reduction of the 2 COUT values
-#pragma unroll
-        for (int i = 0; i < 2 * COUT; ++i) {
-            double s = acc[i];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-            if (lane == 0) lds[i][wave] = s;
-        }
-        __syncthreads();
-        if (threadIdx.x < 2 * COUT) {
-            const double s = lds[threadIdx.x][0] + lds[threadIdx.x][1] + lds[threadIdx.x][2] + lds[threadIdx.x][3];
-            // partials[((p * cin + b) * 2 COUT + i) * nblk + block]
-            partials[((size_t)(p * A.cin + b) * 2 * COUT + threadIdx.x) * gridDim.x + blockIdx.x] = s;
-        }
-        __syncthreads();
-    }
-}
-
-// gW[p][a][b] (float32 complex) from the partials, in a fixed order.
-__global__ void wgrad_finish_kernel(const double* __restrict__ partials, int nblk, int cin, int cout, float2* __restrict__ gW)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;   // over (p, b, a)
-    if (i >= 9 * cin * cout) return;
-    const int p = i / (cin * cout);
-    const int r = i - p * cin * cout;
-    const int b = r / cout, a = r - b * cout;
-    double re = 0.0, im = 0.0;
-    const double* pr = partials + ((size_t)(p * cin + b) * 2 * cout + 2 * a) * nblk;
-    const double* pi = pr + nblk;
-    for (int k = 0; k < nblk; ++k) {
-        re += pr[k];
-        im += pi[k];
-    }
-    gW[(p * cout + a) * cin + b] = make_float2((float)re, (float)im);
-}
-
 // ---- spinor (float32 packed) <-> 4-channel features ----------------------------
 // even_only: the spinor is one EVEN half field; odd sites read as zero and are not written.
 __global__ void spinor_features_kernel(const char* spinor, float2* feat, int Vh, int ps, int nsamples, bool to_features,
@@ -393,6 +282,7 @@ __global__ void feature_pack_kernel(double* canon, float2* feat, Geom g, int C, 
 // B[4 (l / 16) + q][l % 16] and D[4 (l / 16) + q][l % 16] for q = 0..3.
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
@@ -410,6 +300,340 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---- weight gradients on the float64 matrix cores ----------------------------------------
+// gW[p, a, b] = sum_x sum_c gout^a(x)_c conj((T_p in^b)(x)_c) is per path a product of two
+// matrices over K = (site, colour): 16 rows (channel, re/im) of one field against 16 columns
+// (channel, re/im) of the other, transported one; the four real products of a complex one are the
+// four entries of a 2 x 2 block.  The side with fewer channels is the transported one: with the
+// sites renumbered, gout^a conj(T_p in^b) summed over x is (T_p' gout^a) conj(in^b) with the
+// opposite hop p', so either side can be.  With at most four transported channels two paths share
+// one product (columns 0..7 and 8..15), with at most two, four.
+//
+// A wave covers 64 sites of one parity.  It stages the untransported field once through LDS into
+// matrix operands that stay in registers (48 per lane), then per path transports the other field
+// (one site per lane, float32 as the forward layer does it), stages it and issues 48
+// v_mfma_f64_16x16x4: float32 factors, exact products, float64 sums over everything.  Operand
+// layout: lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and D[4 q + l / 16][l % 16], q = 0..3.
+// The loads of the next path are in flight during the products.
+//
+// Bound by the vector and matrix units together: on this chip the float64 and float32 matrix
+// products keep a SIMD's vector unit busy (measured: a 16x16x4 float64 product 65 cycles, float32 33,
+// each float32 FMA beside them 5 more, also from other waves).  float32 products would need their
+// sums moved to float64 every four terms to be as exact as the sum over one site's six was, eight
+// float64 instructions a product, and come out even.  Per wave and path: 48 products with 96
+// conversions (3600 cycles), 288 FMAs of the transports and ~300 other instructions (3000).
+// 8 -> 8 channels, 8 samples on 16^3 x 32: 427 us, against 1930 us for a vector kernel that walked
+// the sites once per path and input channel; 4 -> 8: 255 us against 1590 us.  At 512 sites (one
+// workgroup's work) the launch and its sum take 14 us whatever the channels, against 46 us for
+// 8 -> 8 and 7 us for 1 -> 2 before.
+struct WgArgs {
+    const char* gauge;      // packed float32 links
+    const float2* raw;      // the field that is not transported, craw channels
+    const float2* tr;       // the transported field, ctr channels
+    Geom g;
+    int craw, ctr;
+    long long raw_sample, tr_sample;   // float2 elements between samples
+    int gpp;                // 64-site groups per parity
+    int ngroups;            // of all samples and parities
+    double* partials;       // [unit][workgroup][256]
+};
+
+constexpr int WG_LD = 20;      // floats per staged row: 16 columns + 4 of padding (conflict-free)
+constexpr int WG_WAVES = 8;    // waves per workgroup
+constexpr int wg_units(int tc) { return (9 * tc + 7) / 8; }   // products of all nine paths
+
+// Neighbour features (and the link) of one path as loaded.
+template <int R, int TC> struct WgRaw {
+    float4 l[R == 12 ? 3 : 4];
+    float2 l18;
+    float2 v[TC][3];
+    float sign;
+    bool edges;   // the path's direction has a boundary sign other than +1
+};
+
+// Neighbour of a site along a path known at run time only (1..4: +x..+t, 5..8: -x..-t; the same
+// for a whole wave) and whether the hop crosses the lattice edge.
+__device__ __forceinline__ uint32_t path_neighbour(const Geom& g, uint32_t cb, const int c[4], int path, bool* edge)
+{
+    switch (path) {
+    case 1: *edge = on_boundary<0, true>(g, c); return neighbour<0, true>(g, cb, c);
+    case 2: *edge = on_boundary<1, true>(g, c); return neighbour<1, true>(g, cb, c);
+    case 3: *edge = on_boundary<2, true>(g, c); return neighbour<2, true>(g, cb, c);
+    case 4: *edge = on_boundary<3, true>(g, c); return neighbour<3, true>(g, cb, c);
+    case 5: *edge = on_boundary<0, false>(g, c); return neighbour<0, false>(g, cb, c);
+    case 6: *edge = on_boundary<1, false>(g, c); return neighbour<1, false>(g, cb, c);
+    case 7: *edge = on_boundary<2, false>(g, c); return neighbour<2, false>(g, cb, c);
+    default: *edge = on_boundary<3, false>(g, c); return neighbour<3, false>(g, cb, c);
+    }
+}
+
+template <int R, int TC>
+__device__ __forceinline__ void wg_load(const WgArgs& A, int path, const float2* tr, int par, uint32_t cb, const int c[4],
+                                        WgRaw<R, TC>& x)
+{
+    const int Vh = A.g.Vh;
+    uint32_t src = cb;
+    int spar = par;
+    if (path > 0) {
+        const int mu = (path - 1) & 3;
+        const bool fwd = path <= 4;
+        bool edge;
+        const uint32_t nb = path_neighbour(A.g, cb, c, path, &edge);
+        x.edges = A.g.bcf[mu] != 1.0f;
+        x.sign = edge ? A.g.bcf[mu] : 1.0f;
+        const int lpar = fwd ? par : 1 - par;
+        const uint32_t ls = fwd ? cb : nb;
+        const char* grp = A.gauge + (size_t)(2 * mu + lpar) * link_site_bytes(P_F32, R) * A.g.ps;
+#pragma unroll
+        for (int k = 0; k < (R == 12 ? 3 : 4); ++k) x.l[k] = ld32<float4>(grp + (size_t)k * A.g.ps * 16, ls);
+        if constexpr (R == 18) x.l18 = ld32<float2>(grp + (size_t)4 * A.g.ps * 16, ls);
+        src = nb;
+        spar = 1 - par;
+    }
+    const float2* site = tr + (size_t)spar * 3 * Vh;
+#pragma unroll
+    for (int b = 0; b < TC; ++b)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            x.v[b][k] = ld32<float2>(site + (size_t)((b < A.ctr ? b : A.ctr - 1) * 6 + k) * Vh, src);
+}
+
+// T_p of the loaded features into the wave's staging rows (colour, site), columns col0 ..
+template <int R, int TC>
+__device__ __forceinline__ void wg_stage(int path, int lane, float* S, int col0, const WgRaw<R, TC>& x)
+{
+    if (path == 0) {
+#pragma unroll
+        for (int b = 0; b < TC; b += 2)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                *(float4*)&S[(k * 64 + lane) * WG_LD + col0 + 2 * b] =
+                    make_float4(x.v[b][k].x, x.v[b][k].y, x.v[b + 1][k].x, x.v[b + 1][k].y);
+        return;
+    }
+    float u[18];
+#pragma unroll
+    for (int k = 0; k < (R == 12 ? 3 : 4); ++k) {
+        u[4 * k] = x.l[k].x; u[4 * k + 1] = x.l[k].y; u[4 * k + 2] = x.l[k].z; u[4 * k + 3] = x.l[k].w;
+    }
+    if constexpr (R == 18) {
+        u[16] = x.l18.x;
+        u[17] = x.l18.y;
+    } else {
+        reconstruct_row2(u);
+    }
+    if (path > 4) {   // U^dagger in place
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = a; b < 3; ++b) {
+                const float re = u[2 * (3 * a + b)], im = u[2 * (3 * a + b) + 1];
+                u[2 * (3 * a + b)] = u[2 * (3 * b + a)];
+                u[2 * (3 * a + b) + 1] = -u[2 * (3 * b + a) + 1];
+                if (a != b) {
+                    u[2 * (3 * b + a)] = re;
+                    u[2 * (3 * b + a) + 1] = -im;
+                }
+            }
+    }
+    if (x.edges) {
+#pragma unroll
+        for (int i = 0; i < 18; ++i) u[i] *= x.sign;
+    }
+#pragma unroll
+    for (int b = 0; b < TC; b += 2) {
+        float t[2][6];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float v[6];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                v[2 * k] = x.v[b + h][k].x;
+                v[2 * k + 1] = x.v[b + h][k].y;
+            }
+            mat_vec(u, v, t[h], false);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            *(float4*)&S[(k * 64 + lane) * WG_LD + col0 + 2 * b] =
+                make_float4(t[0][2 * k], t[0][2 * k + 1], t[1][2 * k], t[1][2 * k + 1]);
+    }
+}
+
+// Rows of a lane past the last site: zeros on both sides, so they add nothing.
+__device__ __forceinline__ void wg_zero_rows(float* S, int lane)
+{
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int h = 0; h < 16; h += 4) *(float4*)&S[(k * 64 + lane) * WG_LD + h] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
+// Units u0 .. u0 + N - 1 of the wave's groups.  Unit u is the 8 / TC paths from path 8 / TC u on
+// (path 9 and up do not exist).  Channels past a field's own repeat its last one, and columns that
+// nothing was staged into hold what was there: each only reaches entries of D that are never read.  The loop over units is a real
+// one, its direction known at run time only: unrolled over the paths the code is larger than the
+// instruction cache (64 KB), and a wave walks it once per group.
+template <int N, int R, int TC>
+__device__ __forceinline__ void wg_run(const WgArgs& A, int u0, float* lds)
+{
+    constexpr int NP = 8 / TC;   // paths per unit
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float* S = lds + wave * 192 * WG_LD;
+    const uint32_t Vh = (uint32_t)A.g.Vh;
+    f64x4 acc[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+    // contiguous runs of groups per wave, workgroups in XCD-contiguous order; consecutive groups are
+    // the even and odd sites of one range.  (An XCD's waves walking one run side by side instead
+    // took the same time within 2%.)
+    const long long nw = (long long)gridDim.x * WG_WAVES;
+    const long long w = (long long)xcd_remap(blockIdx.x, gridDim.x) * WG_WAVES + wave;
+    const int g1 = __builtin_amdgcn_readfirstlane((int)(A.ngroups * (w + 1) / nw));
+    for (int gi = __builtin_amdgcn_readfirstlane((int)(A.ngroups * w / nw)); gi < g1; ++gi) {
+        const int n = gi / (2 * A.gpp), r = gi - n * 2 * A.gpp;
+        const int par = r & 1;
+        const uint32_t i = (uint32_t)(r >> 1) * 64 + lane;
+        const bool valid = i < Vh;
+        const uint32_t cb = valid ? i : 0;   // lanes past the end stay in bounds; their rows are zeroed
+        int c[4];
+        cb_coords(A.g, cb, par, c);
+        const float2* tr = A.tr + (size_t)n * A.tr_sample;
+        const float2* site = A.raw + (size_t)n * A.raw_sample + (size_t)par * 3 * Vh;
+        WgRaw<R, TC> x[NP];
+        float raw[48];
+        {
+            float2 v[8][3];
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    v[b][k] = ld32<float2>(site + (size_t)((b < A.craw ? b : A.craw - 1) * 6 + k) * Vh, cb);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int b = 0; b < 8; b += 2)
+                    *(float4*)&S[(k * 64 + lane) * WG_LD + 2 * b] =
+                        make_float4(v[b][k].x, v[b][k].y, v[b + 1][k].x, v[b + 1][k].y);
+            if (!valid) wg_zero_rows(S, lane);
+        }
+#pragma unroll
+        for (int h = 0; h < NP; ++h) if (h == 0 || NP * u0 + h < 9) wg_load<R, TC>(A, NP * u0 + h, tr, par, cb, c, x[h]);
+        wave_lds_sync();
+#pragma unroll
+        for (int s = 0; s < 48; ++s) raw[s] = S[(4 * s + (lane >> 4)) * WG_LD + (lane & 15)];
+        wave_lds_sync();
+#pragma unroll 1
+        for (int u = 0; u < N; ++u) {
+#pragma unroll
+            for (int h = 0; h < NP; ++h) {
+                if (h > 0) __builtin_amdgcn_sched_barrier(0);   // one transport's registers at a time
+                const int path = NP * (u0 + u) + h;
+                if (h == 0 || path < 9) wg_stage<R, TC>(path, lane, S, 2 * TC * h, x[h]);
+            }
+            if (!valid) wg_zero_rows(S, lane);
+            wave_lds_sync();
+            if (u + 1 < N) {
+#pragma unroll
+                for (int h = 0; h < NP; ++h) {
+                    const int path = NP * (u0 + u + 1) + h;
+                    if (h == 0 || path < 9) wg_load<R, TC>(A, path, tr, par, cb, c, x[h]);
+                }
+            }
+            // eight column entries are read ahead of the eight products under way, so that the
+            // products do not wait for the LDS one by one
+            f64x4 t = f64x4{0.0, 0.0, 0.0, 0.0};
+            const float* col = S + (lane >> 4) * WG_LD + (lane & 15);
+            float bq[2][8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) bq[0][j] = col[4 * j * WG_LD];
+#pragma unroll
+            for (int s = 0; s < 48; s += 8) {
+                if (s + 8 < 48) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) bq[(s / 8 + 1) & 1][j] = col[4 * (s + 8 + j) * WG_LD];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    asm volatile("" : "+v"(raw[s + j]));   // converted here, not kept as 96 registers of doubles
+                    t = __builtin_amdgcn_mfma_f64_16x16x4f64((double)raw[s + j], (double)bq[(s / 8) & 1][j], t, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (u == k) {   // (the empty asm keeps this a branch, not a selection between all of them)
+                    asm volatile("");
+                    acc[k] += t;
+                }
+        }
+    }
+    // the workgroup's sums, unit by unit, in a fixed order: entry q * 64 + lane holds D[4 q + lane / 16][lane % 16]
+    double* red = (double*)lds;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave * 256 + q * 64 + lane] = acc[u][q];
+        __syncthreads();
+        if (threadIdx.x < 256) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < WG_WAVES; ++k) s += red[k * 256 + threadIdx.x];
+            A.partials[((size_t)(u0 + u) * gridDim.x + blockIdx.x) * 256 + threadIdx.x] = s;
+        }
+    }
+}
+
+// SPLIT: one unit per workgroup (grid y) instead of all of them.
+template <int R, int TC, bool SPLIT>
+__global__ void __launch_bounds__(64 * WG_WAVES, 2) ptconv_wgrad_kernel(WgArgs A)
+{
+    __shared__ __attribute__((aligned(16))) float lds[WG_WAVES * 192 * WG_LD];
+    if constexpr (SPLIT) wg_run<1, R, TC>(A, blockIdx.y, lds);
+    else wg_run<wg_units(TC), R, TC>(A, 0, lds);
+}
+
+// gW[p][a][b] (float32 complex) from the partials, summed in a fixed order: workgroup (unit, q)
+// takes the 64 entries of rows 4 q .. 4 q + 3 (two channels), 16 threads per entry with four loads
+// in flight each, and combines the 2 x 2 blocks.  raw_gout: gout was the untransported side (the
+// rows); else in was, and a unit's hop p stands for the opposite one.
+__global__ void __launch_bounds__(1024) wgrad_finish_kernel(const double* __restrict__ partials, int nblk, int cin,
+                                                            int cout, int tc, bool raw_gout, float2* __restrict__ gW)
+{
+    __shared__ double part[16][64];
+    const int unit = blockIdx.x, q = blockIdx.y, e = threadIdx.x & 63, j = threadIdx.x >> 6;
+    const double* p = partials + (size_t)unit * nblk * 256 + q * 64 + e;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int k = j;
+    for (; k + 48 < nblk; k += 64)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += p[(size_t)(k + 16 * i) * 256];
+    for (; k < nblk; k += 16) s[0] += p[(size_t)k * 256];
+    part[j][e] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;   // the first wave alone from here on
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t += part[i][e];
+    part[0][e] = t;
+    wave_lds_sync();
+    // lane: row channel 2 q + (e >> 5), column (path, channel) from the other bits
+    const int rc = 2 * q + (e >> 5), col = e & 7, npath = 8 / tc;
+    if ((e >> 3 & 3) != 0) return;   // eight column pairs per row pair
+    const int h = col / tc, cc = col - h * tc, path = npath * unit + h;
+    if (path > 8 || rc >= (raw_gout ? cout : cin) || cc >= (raw_gout ? cin : cout)) return;
+    const double* D = &part[0][(e >> 5) * 32 + 2 * col];   // [row parity][column parity], rows 16 apart
+    const double d00 = D[0], d01 = D[1], d10 = D[16], d11 = D[17];
+    const double re = d00 + d11;                            // g conj(t), or t conj(in) with the sides swapped
+    const double im = raw_gout ? d10 - d01 : d01 - d10;
+    const int a = raw_gout ? rc : cc, b = raw_gout ? cc : rc;
+    const int pw = raw_gout || path == 0 ? path : (path <= 4 ? path + 4 : path - 4);
+    gW[(pw * cout + a) * cin + b] = make_float2((float)re, (float)im);
 }
 
 // One path in two halves so that the loads of path p + 1 are in flight while path p is
@@ -886,15 +1110,35 @@ wd_status launch_spinor_features(wd_context ctx, const Geom& g, int nsamples, vo
 
 static bool ok_channels(int c) { return c == 1 || c == 2 || c == 3 || c == 4 || c == 8; }
 
-template <int R>
-static wd_status wgrad_r(wd_context ctx, const PTArgs& A, int cout, const void* gout, int nsamples, int nblk, double* part)
+// A 256-CU chip holds 2048 of the kernel's waves at once (two per SIMD, 120 KB of LDS per
+// workgroup), so a launch takes as many rounds as its waves go over 2048.  A wave with all units takes
+// 50-60 us per group (8 -> 8), one with a single unit about 14 us, as it stages the untransported
+// field and waits for its first loads each time: the split pays with few groups.  Measured, 8 -> 8:
+// 420 groups 30 us split and 65 us whole, 1368 groups 80 and 68; 4 -> 8: 24 and 37, 41 and 41.
+constexpr int WG_SLOTS = 2048;
+
+static bool wgrad_split(long long ngroups, int tc)
 {
-    dim3 grid(nblk, 9), block(256);
-    switch (cout) {
-#define WD_PT(C) case C: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, C>), grid, block, 0, ctx->stream, A, (const float2*)gout, nsamples, part); break;
-        WD_PT(1) WD_PT(2) WD_PT(3) WD_PT(4) WD_PT(8)
-#undef WD_PT
-    default: set_error("ptconv: C_out = %d not supported", cout); return WD_EUNSUPPORTED;
+    const long long whole = (ngroups + WG_SLOTS - 1) / WG_SLOTS;
+    const long long units = (ngroups * wg_units(tc) + WG_SLOTS - 1) / WG_SLOTS;
+    return 0.28 * (double)units < (double)whole;
+}
+
+template <int R>
+static wd_status wgrad_r(wd_context ctx, WgArgs& A, int tc, int* nblk, double** part)
+{
+    const bool split = wgrad_split(A.ngroups, tc);
+    *nblk = ((A.ngroups < WG_SLOTS ? A.ngroups : WG_SLOTS) + WG_WAVES - 1) / WG_WAVES;
+    WD_TRY(ws_get(ctx, "ptconv.partials", (size_t)wg_units(tc) * *nblk * 256 * sizeof(double), (void**)part));
+    A.partials = *part;
+    const dim3 grid(*nblk, split ? wg_units(tc) : 1), block(64 * WG_WAVES);
+    switch (tc + (split ? 1 : 0)) {
+    case 2: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 2, false>), grid, block, 0, ctx->stream, A); break;
+    case 3: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 2, true>), grid, block, 0, ctx->stream, A); break;
+    case 4: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 4, false>), grid, block, 0, ctx->stream, A); break;
+    case 5: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 4, true>), grid, block, 0, ctx->stream, A); break;
+    case 8: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 8, false>), grid, block, 0, ctx->stream, A); break;
+    default: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 8, true>), grid, block, 0, ctx->stream, A); break;
     }
     WD_LAUNCHED();
     return WD_OK;
@@ -1012,25 +1256,30 @@ wd_status wd_ptconv_backward(wd_gauge g, int cin, int cout, wd_prec wprec, int n
     if (gW) {
         const void* links;
         WD_TRY(gauge_links(g, WD_F32, &links));
-        PTArgs A;
+        // the side with fewer channels is transported
+        const bool raw_gout = cin <= cout;
+        WgArgs A{};
         A.gauge = (const char*)links;
-        A.in = (const float2*)in;
-        A.out = nullptr;
-        A.W = W;
         A.g = g->geom;
-        A.cin = cin;
-        A.in_sample = (long long)cin * 6 * g->geom.Vh;
-        A.out_sample = (long long)cout * 6 * g->geom.Vh;
-        const long long nsites = 2ll * g->geom.Vh * nsamples;
-        long long nblk = (nsites + 255) / 256;
-        if (nblk > 512) nblk = 512;
-        void* part;
-        WD_TRY(ws_get(ctx, "ptconv.partials", (size_t)9 * cin * 2 * cout * nblk * sizeof(double), &part));
-        WD_TRY(g->recon == 12 ? wgrad_r<12>(ctx, A, cout, gout, nsamples, (int)nblk, (double*)part)
-                              : wgrad_r<18>(ctx, A, cout, gout, nsamples, (int)nblk, (double*)part));
-        const int n = 9 * cin * cout;
-        hipLaunchKernelGGL(wgrad_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, (const double*)part,
-                           (int)nblk, cin, cout, (float2*)gW);
+        A.raw = (const float2*)(raw_gout ? gout : in);
+        A.tr = (const float2*)(raw_gout ? in : gout);
+        A.craw = raw_gout ? cout : cin;
+        A.ctr = raw_gout ? cin : cout;
+        A.raw_sample = (long long)A.craw * 6 * g->geom.Vh;
+        A.tr_sample = (long long)A.ctr * 6 * g->geom.Vh;
+        A.gpp = (g->geom.Vh + 63) / 64;
+        const long long ngroups = 2ll * A.gpp * nsamples;
+        if (ngroups >= (1ll << 31)) {
+            set_error("wd_ptconv_backward: %d samples of this lattice are too many for one call", nsamples);
+            return WD_ESHAPE;
+        }
+        A.ngroups = (int)ngroups;
+        const int tc = A.ctr <= 2 ? 2 : (A.ctr <= 4 ? 4 : 8);
+        int nblk;
+        double* part;
+        WD_TRY(g->recon == 12 ? wgrad_r<12>(ctx, A, tc, &nblk, &part) : wgrad_r<18>(ctx, A, tc, &nblk, &part));
+        hipLaunchKernelGGL(wgrad_finish_kernel, dim3(wg_units(tc), 4), dim3(1024), 0, ctx->stream, (const double*)part,
+                           nblk, cin, cout, tc, raw_gout, (float2*)gW);
         WD_LAUNCHED();
     }
     return WD_OK;

@@ -321,6 +321,28 @@ template <bool NT> __device__ __forceinline__ uint32_t ldv(const uint32_t* p)
     else return *p;
 }
 
+// Element i of a plane whose base is the same for the whole wave: a scalar base and a 32-bit byte
+// offset in one vector register.  The empty constraint keeps the base a scalar pair of its own;
+// left alone, the compiler adds the offset to one plane's base and derives the other planes'
+// addresses from that with 64-bit vector sums, two instructions per load.  Planes stay below 4 GiB:
+// 2^28 sites of 16 bytes, whose canonical links alone (309 GB) exceed the card's memory.
+template <typename V, bool NT = false> __device__ __forceinline__ V ld32(const void* plane, uint32_t i)
+{
+    typedef const __attribute__((address_space(1))) char* gptr;
+    typedef typename ExtVec<V>::T E;
+    uint64_t p = (uint64_t)plane;
+    asm("" : "+s"(p));
+    const __attribute__((address_space(1))) E* q =
+        (const __attribute__((address_space(1))) E*)((gptr)p + (uint32_t)(i * (uint32_t)sizeof(V)));
+    E r;
+    if constexpr (NT) r = __builtin_nontemporal_load(q);
+    else r = *q;
+    V v;
+    static_assert(sizeof(v) == sizeof(r), "vector size");
+    __builtin_memcpy(&v, &r, sizeof(v));
+    return v;
+}
+
 template <typename T> __device__ __forceinline__ void reconstruct_row2(T* u)
 {
     // row2 = conj(row0 x row1)

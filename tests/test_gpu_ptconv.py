@@ -228,3 +228,41 @@ def test_matrix_core_wave_orders_agree(cin, cout, monkeypatch):
     assert orc.rel_l2(got[0], orc.ptconv_forward(U, phi[0], Wref.astype(np.complex128), BC)) < 1e-2
     g.close()
     ctx.close()
+
+@pytest.mark.parametrize("dims,cin,cout,n,recon", [
+    ((2, 2, 2, 2), 8, 8, 1, 12),        # 8 sites per parity: one partial group, split launch
+    ((8, 4, 4, 4), 8, 8, 1, 18),        # whole groups exactly
+    ((4, 6, 2, 10), 8, 3, 3, 18),       # transported output side, paired paths, repeated channels
+    ((4, 6, 2, 10), 1, 8, 2, 12),
+    ((4, 6, 2, 10), 4, 4, 1, 12),
+    ((10, 8, 6, 6), 8, 8, 90, 12),      # 2070 groups: just past one round of the chip
+    ((8, 8, 8, 8), 4, 8, 61, 12),       # 3904 groups, whole launch, two groups per wave
+])
+def test_weight_gradient_launch_shapes(dims, cin, cout, n, recon):
+    """The weight gradient at the edges of its 64-site groups, its split and its whole launch, and
+    with either side transported, against the oracle.  Each of the float32 transports it sums in
+    float64 is within ~10 roundings of 2^-24 (link rebuild, six-term sums), so 1e-5 leaves an order
+    of magnitude for cancellation."""
+    import torch
+    from paper_0810_5365_amd import wdirac as w
+    X, Y, Z, T = dims
+    ctx = w.Context(0)
+    U = ls.gauge_field(dims, 0.7, 5011)
+    g = w.Gauge(ctx, dims, BC, recon)
+    g.upload(U)
+    lat = w.lattice(dims, BC)
+    distinct = min(n, 3)   # the oracle sees three samples; the others repeat them
+    phi = ls.gaussian_complex((distinct, cin, T, Z, Y, X, 3), 301)
+    gout = ls.gaussian_complex((distinct, cout, T, Z, Y, X, 3), 302)
+    idx = np.arange(n) % distinct
+    fin = w.pack_features(ctx, lat, phi[idx], cin, n)
+    fgo = w.pack_features(ctx, lat, gout[idx], cout, n)
+    W = torch.zeros((9, cout, cin, 2), dtype=torch.float32, device="cuda")
+    gW = torch.full((9, cout, cin, 2), float("nan"), dtype=torch.float32, device="cuda")
+    w.wd_ptconv_backward(g.handle, cin, cout, w.F32, n, W.data_ptr(), fin.data_ptr(), fgo.data_ptr(), None,
+                         gW.data_ptr())
+    got = gW.cpu().numpy().astype(np.float64)
+    ref = sum((idx == s).sum() * orc.ptconv_backward_weight(U, phi[s], gout[s], BC) for s in range(distinct))
+    assert orc.rel_l2(got[..., 0] + 1j * got[..., 1], ref) < 1e-5
+    g.close()
+    ctx.close()
