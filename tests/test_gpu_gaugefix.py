@@ -105,3 +105,33 @@ def test_solve_in_fixed_gauge(fixed):
     xp = w.unpack(ctx, lat, w.FULL, w.F64, fx, b.shape)
     x = np.einsum("tzyxba,tzyxsb->tzyxsa", np.conj(Om), xp)       # back to the original gauge
     assert orc.rel_residual(lambda v: orc.apply_m(U, v, kappa, BC), x, b) <= 1.05 * tol
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 2, 4, 2), (2, 8, 6, 14), (10, 4, 6, 4)])
+def test_rotation_at_the_edges_of_its_launches(dims):
+    """Extents of two (every hop wraps), site counts that fill no workgroup of either kernel, and a
+    second upload in between: Omega against the product of the links in numpy (T - 1 products of
+    unitary matrices: below 1e-13), the float64 dslash against the oracle on the rotated links."""
+    from paper_0810_5365_amd import wdirac as w
+    ctx = w.Context(0)
+    X, Y, Z, T = dims
+    lat = w.lattice(dims, BC)
+    g = w.Gauge(ctx, dims, BC, 18)
+    psi = ls.gaussian_complex((X * Y * Z * T // 2, 4, 3), 6, ls.STREAM_SPINOR)
+    for seed in (78, 79):
+        U = ls.gauge_field(dims, 0.6, seed)
+        g.upload(U)
+        g.prepare(w.F64)
+        Om = np.full((T, Z, Y, X, 3, 3), np.nan, dtype=np.complex128)
+        w.wd_gauge_fix_temporal(g.handle, Om.ctypes.data)
+        ref = [np.broadcast_to(np.eye(3, dtype=complex), U[3][0].shape)]
+        for t in range(T - 1):
+            ref.append(ref[t] @ U[3][t])
+        assert np.abs(Om - np.stack(ref)).max() < 1e-13
+        fin = w.pack(ctx, lat, w.ODD, w.F64, psi)
+        fo = w.new_field(lat, w.EVEN, w.F64)
+        w.wd_dslash(g.handle, w.EVEN, 0, w.F64, 1, fin.data_ptr(), fo.data_ptr())
+        got = w.unpack(ctx, lat, w.EVEN, w.F64, fo, psi.shape)
+        assert orc.rel_l2(got, orc.d_eo(transform(U, Om), psi, BC)) < 1e-12
+    g.close()
+    ctx.close()
