@@ -403,7 +403,7 @@ wd_status wd_ptnet_apply_even(wd_gauge g, int nlayers, const int* widths, const 
  * site traversal of depth zb dividing Z and, for nrhs > 1, right-hand sides
  * interleaved with the site tiles; for 16-bit storage with 12-real links and a
  * multiple of 16 rhs also the kernel that runs the colour multiply of 16 rhs on
- * the matrix cores), for both
+ * the matrix cores; and the kernel with four waves per 64 sites), for both
  * dagger settings with and without the fused a x + b D in, and keep the
  * fastest in the context's tuning table.  If cache_path is not NULL the file
  * is read first and the whole table written back after.  Synchronous; uses
@@ -421,7 +421,10 @@ int wd_tune_get(wd_context ctx, const char* key, int* out6);
 int wd_tune_get_n(wd_context ctx, const char* key, int* out, int n);
 
 /* ---- environment overrides (measurement and testing; results do not change, except as noted) ----
- * WD_DSLASH_BLOCK, _REMAP, _NT, _PF, _RHS_INNER, _ZB  launch shape of an untuned dslash
+ * WD_DSLASH_BLOCK, _REMAP, _NT, _PF, _RHS_INNER, _ZB  launch shape of an untuned dslash (all but
+ *                          _NT ask for the kernel with one wave per 64 sites)
+ * WD_DSLASH_SPLIT = 0 / 1  an untuned dslash with one / four waves per 64 sites (default: by size,
+ *                          precision and number of rhs)
  * WD_DSLASH_MFMA = 0 / 1   16-bit multi-rhs dslash off / on the matrix cores, tuned or not
  * WD_BATCH_BLOCK, _WAVES, _PF  force the batch launch shape (tile width 64..256, waves per
  *                          compute unit, pipelined directions 0 / 1) instead of tuning it

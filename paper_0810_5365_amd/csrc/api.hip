@@ -112,12 +112,20 @@ TuneParam tune_lookup(wd_context ctx, const std::string& key)
     }
     TuneParam tp;
     if (mf) tp.mf = atoi(mf);
-    if (const char* e = getenv("WD_DSLASH_BLOCK")) tp.block = atoi(e);
-    if (const char* e = getenv("WD_DSLASH_REMAP")) tp.remap = atoi(e);
+    // a launch shape asked for is one of the plain kernel's
+    auto forced = [&](const char* name, int* v) {
+        if (const char* e = getenv(name)) {
+            *v = atoi(e);
+            tp.split = 0;
+        }
+    };
+    forced("WD_DSLASH_BLOCK", &tp.block);
+    forced("WD_DSLASH_REMAP", &tp.remap);
     if (const char* e = getenv("WD_DSLASH_NT")) tp.nt = atoi(e);
-    if (const char* e = getenv("WD_DSLASH_PF")) tp.pf = atoi(e);
-    if (const char* e = getenv("WD_DSLASH_RHS_INNER")) tp.rhs_inner = atoi(e);
-    if (const char* e = getenv("WD_DSLASH_ZB")) tp.zb = atoi(e);
+    forced("WD_DSLASH_PF", &tp.pf);
+    forced("WD_DSLASH_RHS_INNER", &tp.rhs_inner);
+    forced("WD_DSLASH_ZB", &tp.zb);
+    if (const char* e = getenv("WD_DSLASH_SPLIT")) tp.split = atoi(e);
     return tp;
 }
 

@@ -41,8 +41,8 @@ __global__ void __launch_bounds__(256) batch_kernel(const BatchItem* __restrict_
         const int rhs = (int)(local % B.nrhs);
         const uint32_t cb = (uint32_t)(local / B.nrhs) * blockDim.x + threadIdx.x;
         if (cb < (uint32_t)B.A.g.Vh) {
-            if (B.dagger) dslash_site<P, R, true, false, NT, PF>(B.A, cb, rhs);
-            else dslash_site<P, R, false, false, NT, PF>(B.A, cb, rhs);
+            if (B.dagger) dslash_site<P, R, true, false, NT, PF, 0, HopRawWide<P, R>>(B.A, cb, rhs);
+            else dslash_site<P, R, false, false, NT, PF, 0, HopRawWide<P, R>>(B.A, cb, rhs);
         }
     }
 }

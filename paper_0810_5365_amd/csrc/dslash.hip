@@ -13,18 +13,28 @@ __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs A)
     uint32_t bid = A.remap ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
     int rhs = blockIdx.y;
     if (A.rhs_inner > 1) {
-        rhs = (int)(bid % (uint32_t)A.rhs_inner);
-        bid /= (uint32_t)A.rhs_inner;
+        const uint32_t q = fdiv(bid, A.drhs);
+        rhs = (int)(bid - q * (uint32_t)A.rhs_inner);
+        bid = q;
     }
     const uint32_t i = bid * blockDim.x + threadIdx.x;
     if (i >= (uint32_t)A.g.Vh) return;
-    if (A.zb > 0) {
-        int c[4];
-        const uint32_t cb = zblock_site(A, i, c);
-        dslash_site<P, R, DAG, XPAY, NT, PF>(A, cb, c, rhs);
-    } else {
-        dslash_site<P, R, DAG, XPAY, NT, PF>(A, i, rhs);
+    dslash_at<P, R, DAG, XPAY, NT, PF>(A, i, rhs);
+}
+
+// Four waves per 64 sites (dslash_split).
+template <int P, int R, bool DAG, bool XPAY, bool NT>
+__global__ void __launch_bounds__(256) dslash_split_kernel(DslashArgs A)
+{
+    __shared__ float4 lds[dslash_split_lds(P) / sizeof(float4)];
+    uint32_t group = A.remap ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+    int rhs = blockIdx.y;
+    if (A.rhs_inner > 1) {
+        const uint32_t q = fdiv(group, A.drhs);
+        rhs = (int)(group - q * (uint32_t)A.rhs_inner);
+        group = q;
     }
+    dslash_split<P, R, DAG, XPAY, NT>(A, group, rhs, lds);
 }
 
 template <int P, int R, bool DAG, bool XPAY, bool NT, bool PF>
@@ -41,6 +51,17 @@ static wd_status run(wd_context ctx, const DslashArgs& A, int nrhs, const TunePa
 template <int P, int R>
 static wd_status dispatch_pr(wd_context ctx, const DslashArgs& A, const DslashCall& c, const TuneParam& tp)
 {
+    if (tp.split) {
+        const unsigned ngrp = (A.g.Vh + 63) / 64;
+        const dim3 grid = A.rhs_inner > 1 ? dim3(ngrp * (unsigned)c.nrhs) : dim3(ngrp, c.nrhs), block(256);
+        switch ((c.dagger ? 1 : 0) | (c.x ? 2 : 0) | (tp.nt ? 4 : 0)) {
+#define WD_SP(K) case K: hipLaunchKernelGGL((dslash_split_kernel<P, R, (K & 1) != 0, (K & 2) != 0, (K & 4) != 0>), grid, block, 0, ctx->stream, A); break;
+        WD_SP(0) WD_SP(1) WD_SP(2) WD_SP(3) WD_SP(4) WD_SP(5) WD_SP(6) WD_SP(7)
+#undef WD_SP
+        }
+        WD_LAUNCHED();
+        return WD_OK;
+    }
     const int sel = (c.dagger ? 1 : 0) | (c.x ? 2 : 0) | (tp.nt ? 4 : 0) | (tp.pf ? 8 : 0);
     switch (sel) {
 #define WD_DS(K) case K: return run<P, R, (K & 1) != 0, (K & 2) != 0, (K & 4) != 0, (K & 8) != 0>(ctx, A, c.nrhs, tp);
@@ -75,6 +96,7 @@ wd_status dslash_setup(const Geom& g, const DslashCall& c, const TuneParam& tp, 
         A.xnt = xnt;
     }
     A.rhs_inner = (tp.rhs_inner && c.nrhs > 1) ? c.nrhs : 0;
+    A.drhs = make_fastdiv((uint32_t)c.nrhs);
     A.gf = c.gf;
     A.zb = 0;
     if (tp.zb > 0 && tp.zb < g.L[2] && g.L[2] % tp.zb == 0) {
@@ -82,13 +104,42 @@ wd_status dslash_setup(const Geom& g, const DslashCall& c, const TuneParam& tp, 
         A.dzb = make_fastdiv((uint32_t)tp.zb);
         A.dt = make_fastdiv((uint32_t)g.L[3]);
     }
-    if ((long long)((g.Vh + tp.block - 1) / tp.block) * c.nrhs >= (1ll << 31)) A.rhs_inner = 0;
+    if ((long long)((g.Vh + 63) / 64) * c.nrhs >= (1ll << 31)) A.rhs_inner = 0;
     *out = A;
     return WD_OK;
 }
 
-wd_status launch_dslash_tuned(wd_context ctx, const Geom& g, const DslashCall& c, const TuneParam& tp)
+// What an untuned launch shape leaves open.  us per launch inside Mhat^dag Mhat, one MI355X.
+//
+// Four waves per 64 sites (split) against one: 8^3 x 16 F32 3.9 / 5.4, F64 4.9 / 5.9; 16^3 x 32 F32
+// 8.5 / 8.8, F16 6.7 / 7.3, BF16 6.2 / 7.4, F64 17.2 / 16.9; 24^3 x 48 F32 35.3 / 37.7, F16 21.3 / 22.6,
+// F64 86.8 / 82.8; 28^3 x 56 (9604 groups of 64) F32 74.0 / 75.4, F16 36.2 / 37.8; 32^3 x 64 (16 384
+// groups) F32 116.6 / 116.3, F16 67.4 / 65.2.  It hides latency, at the price of a trip through LDS
+// and, in F64, of fewer bytes in flight per register.  Several rhs: F32 gains throughout (3 on 16^3 x 32
+// 16.5 / 18.2, on 24^3 x 48 97.9 / 99.8, 16 on 16^3 x 32 89.4 / 90.2); 16-bit storage is bound by its
+// vector work once the chip is full (BF16: 3 on 16^3 x 32, 3072 groups in all, 11.7 / 12.0; 3 on
+// 24^3 x 48 47.9 / 45.0; 16 on 16^3 x 32 52.6 / 46.5).
+//
+// Non-temporal link loads leave the 256 MB last-level cache to the spinors; links that fit it beside
+// them are better kept: F32 24^3 x 48 (127 MB of links) 35.3 kept / 40.8 not, 28^3 x 56 (236 MB)
+// 81.8 / 74.0; F16 28^3 x 56 (118 MB) 36.2 / 42.0, 32^3 x 64 (201 MB) 66.8 / 65.2; F64 20^3 x 40
+// (123 MB) 36.4 / 40.7, 24^3 x 48 (255 MB) 91.2 / 82.8.  With several rhs the links are read again
+// within a launch and are kept (16 rhs on 16^3 x 32, F32 90 / 110, BF16 46 / 57).
+constexpr size_t NT_LINK_BYTES = (size_t)160 << 20;
+
+TuneParam dslash_shape(const Geom& g, const DslashCall& c, const TuneParam& tp)
 {
+    TuneParam t = tp;
+    const long long groups = (long long)((g.Vh + 63) / 64) * c.nrhs;
+    const bool one = c.nrhs == 1;
+    if (t.split < 0) t.split = groups <= (c.prec == WD_F64 ? 512 : one ? 12288 : c.prec == WD_F32 ? 32768 : 4096);
+    if (t.nt < 0) t.nt = one && 8 * link_site_bytes(c.prec, c.recon) * (size_t)g.ps > NT_LINK_BYTES;
+    return t;
+}
+
+wd_status launch_dslash_tuned(wd_context ctx, const Geom& g, const DslashCall& c, const TuneParam& shape)
+{
+    const TuneParam tp = dslash_shape(g, c, shape);
     if (tp.mf && mrhs_eligible(c)) return launch_dslash_mrhs(ctx, g, c);
     DslashArgs A;
     WD_TRY(dslash_setup(g, c, tp, &A));

@@ -41,6 +41,7 @@ struct DslashArgs {
     int zb;          // > 0: z-blocked site traversal with this block depth (divides Z)
     int gf;          // links in temporal gauge: U_t = 1 except on the last time slice
     FastDiv dzb, dt; // division by zb and by T for the blocked traversal
+    FastDiv drhs;    // division by the number of rhs for the interleaved order
     double* red;     // per-workgroup partial sums of a fused reduction (dslash_red.hip)
     const char* y;   // the other operand of the fused <y, out>
     const double* coef;   // RED_CGR: the step length alpha, in device memory
@@ -49,6 +50,8 @@ struct DslashArgs {
 
 // Kernel arguments for a launch of the hopping term with launch shape tp (dslash.hip).
 wd_status dslash_setup(const Geom& g, const DslashCall& c, const TuneParam& tp, DslashArgs* A);
+// The launch shape with what it leaves to the rules (link loads, waves per group) settled for this call.
+TuneParam dslash_shape(const Geom& g, const DslashCall& c, const TuneParam& tp);
 
 // v <- the values that storing v at 16-bit precision and loading it back gives (the store's
 // scale and rounding, repeated).
@@ -123,110 +126,105 @@ __device__ __forceinline__ bool unit_link(const DslashArgs& A, const int c[4])
 
 // Loads of direction D: the link (U_mu(x) forward, U_mu(x - mu) backward)
 // and the neighbour spinor.
-template <int D, int P, int R, bool NT, typename T>
+template <int D, bool NT, typename X>
 __device__ __forceinline__ void hop_load(const DslashArgs& A, uint32_t cb, const int c[4], const char* in, size_t gbytes,
-                                         T* u, T* psi)
+                                         X& x)
 {
     constexpr int MU = D >> 1;
     constexpr bool FWD = (D & 1) == 0;
     const uint32_t nb = neighbour<MU, FWD>(A.g, cb, c);
     const int lpar = FWD ? A.par : 1 - A.par;
     const uint32_t lcb = FWD ? cb : nb;
-    if (!unit_link<MU, FWD>(A, c)) LinkIO<P, R, NT>::load(A.gauge + (size_t)(2 * MU + lpar) * gbytes, A.g.ps, lcb, u);
-    SpinorIO<P>::load(in, A.g.ps, nb, psi);
+    if (!unit_link<MU, FWD>(A, c)) x.template load_link<NT>(A.gauge + (size_t)(2 * MU + lpar) * gbytes, A.g.ps, lcb);
+    x.load_spinor(in, A.g.ps, nb);
 }
 
-// Arithmetic of direction D: project, boundary sign, colour multiply, accumulate.
-template <int D, bool DAG, typename T>
-__device__ __forceinline__ void hop_compute(const DslashArgs& A, const int c[4], const T* u, const T* psi, T* acc)
+// Direction D's half spinor: project, boundary sign, colour multiply.
+template <int D, bool DAG, typename X, typename T>
+__device__ __forceinline__ void hop_half_spinor(const DslashArgs& A, const int c[4], const X& x, T* w)
 {
     constexpr int MU = D >> 1;
     constexpr bool FWD = (D & 1) == 0;
     // D: (1 - gamma) on the forward hop, (1 + gamma) on the backward hop; D^dagger swaps them
     constexpr int S = (FWD != DAG) ? -1 : 1;
-    T h[12];
+    T h[12], psi[24];
+    x.spinor(psi);
     project<MU, S>(psi, h);
     T sg;
     if constexpr (sizeof(T) == 8) sg = on_boundary<MU, FWD>(A.g, c) ? A.g.bcd[MU] : 1.0;
     else sg = on_boundary<MU, FWD>(A.g, c) ? A.g.bcf[MU] : 1.0f;
 #pragma unroll
     for (int k = 0; k < 12; ++k) h[k] *= sg;
-    T w[12];
     if (unit_link<MU, FWD>(A, c)) {
 #pragma unroll
         for (int k = 0; k < 12; ++k) w[k] = h[k];
     } else {
+        T u[18];
+        x.link(u);
         su3_mul<!FWD>(u, h, w);
     }
-    accumulate<MU, S>(acc, w);
+}
+
+template <int D, bool DAG, typename T> __device__ __forceinline__ void hop_accumulate(T* acc, const T* w)
+{
+    constexpr int S = (((D & 1) == 0) != DAG) ? -1 : 1;
+    accumulate<(D >> 1), S>(acc, w);
+}
+
+template <int D, bool DAG, typename X, typename T>
+__device__ __forceinline__ void hop_compute(const DslashArgs& A, const int c[4], const X& x, T* acc)
+{
+    T w[12];
+    hop_half_spinor<D, DAG>(A, c, x, w);
+    hop_accumulate<D, DAG>(acc, w);
 }
 
 // One direction at a time: its loads, then its arithmetic, then a fence.
-template <int D, int P, int R, bool DAG, bool NT, typename T>
+template <int D, typename X, bool DAG, bool NT, typename T>
 __device__ __forceinline__ void hop(const DslashArgs& A, uint32_t cb, const int c[4], const char* in, size_t gbytes,
                                     T* acc)
 {
-    T u[18], psi[24];
-    hop_load<D, P, R, NT>(A, cb, c, in, gbytes, u, psi);
-    hop_compute<D, DAG>(A, c, u, psi, acc);
+    X x;
+    hop_load<D, NT>(A, cb, c, in, gbytes, x);
+    hop_compute<D, DAG>(A, c, x, acc);
     order_fence(acc);
 }
 
 // Software-pipelined: the loads of direction D + 1 are issued before the
 // arithmetic of direction D, so each wave keeps two directions in flight.
-template <int D, int P, int R, bool DAG, bool NT, typename T>
+template <int D, bool DAG, bool NT, typename X, typename T>
 __device__ __forceinline__ void hop_pipelined(const DslashArgs& A, uint32_t cb, const int c[4], const char* in,
-                                              size_t gbytes, T* acc, T* u_cur, T* p_cur, T* u_nxt, T* p_nxt)
+                                              size_t gbytes, T* acc, X& cur, X& nxt)
 {
-    if constexpr (D + 1 < 8) hop_load<D + 1, P, R, NT>(A, cb, c, in, gbytes, u_nxt, p_nxt);
+    if constexpr (D + 1 < 8) hop_load<D + 1, NT>(A, cb, c, in, gbytes, nxt);
     asm volatile("" ::: "memory");
-    hop_compute<D, DAG>(A, c, u_cur, p_cur, acc);
+    hop_compute<D, DAG>(A, c, cur, acc);
     order_fence(acc);
 }
 
-// RED > 0 (with XPAY): the site's values of that fused reduction go to red[0 .. 3).  The
-// output is stored first, so the reduction adds no registers to the store.
-template <int P, int R, bool DAG, bool XPAY, bool NT, bool PF, int RED = 0>
-__device__ __forceinline__ void dslash_site(const DslashArgs& A, uint32_t cb, const int c[4], int rhs,
-                                            double* red = nullptr)
+// What follows the sum over directions: out = a x + b D in, stored.  RED > 0 (with XPAY): the site's
+// values of that fused reduction go to red[0 .. 3).  The output is stored first, so the reduction
+// adds no registers to the store.  XPRE: x has been loaded already.
+template <int P, bool XPAY, int RED, bool XPRE, typename T>
+__device__ __forceinline__ void dslash_finish(const DslashArgs& A, uint32_t cb, int rhs, T* acc, double* red,
+                                              const T* xpre = nullptr)
 {
-    using T = typename RealOf<P>::T;
-    const size_t gbytes = link_site_bytes(P, R) * (size_t)A.g.ps;
-    const char* in = A.in + rhs * A.in_stride;
-    T acc[24];
-#pragma unroll
-    for (int k = 0; k < 24; ++k) acc[k] = 0;
-    if constexpr (PF) {
-        T ua[18], pa[24], ub[18], pb[24];
-        hop_load<0, P, R, NT>(A, cb, c, in, gbytes, ua, pa);
-        hop_pipelined<0, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ua, pa, ub, pb);
-        hop_pipelined<1, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ub, pb, ua, pa);
-        hop_pipelined<2, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ua, pa, ub, pb);
-        hop_pipelined<3, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ub, pb, ua, pa);
-        hop_pipelined<4, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ua, pa, ub, pb);
-        hop_pipelined<5, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ub, pb, ua, pa);
-        hop_pipelined<6, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ua, pa, ub, pb);
-        hop_pipelined<7, P, R, DAG, NT>(A, cb, c, in, gbytes, acc, ub, pb, ua, pa);
-    } else {
-        hop<0, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<1, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<2, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<3, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<4, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<5, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<6, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-        hop<7, P, R, DAG, NT>(A, cb, c, in, gbytes, acc);
-    }
     const T b = (T)A.b;
     T xv[24];
     if constexpr (XPAY) {
-        // x is read once, at the site written: a non-temporal load leaves the last-level cache
-        // to the fields the next launch reads (measured: 0.75% on the Mhat^dag Mhat step)
-        if (A.xnt) SpinorIO<P>::load_nt(A.x + rhs * A.x_stride, A.g.ps, cb, xv);
-        else SpinorIO<P>::load(A.x + rhs * A.x_stride, A.g.ps, cb, xv);
-        const T a = (T)A.a;
+        if constexpr (XPRE) {
 #pragma unroll
-        for (int k = 0; k < 24; ++k) acc[k] = a * xv[k] + b * acc[k];
+            for (int k = 0; k < 24; ++k) xv[k] = xpre[k];
+        } else {
+            // x is read once, at the site written: a non-temporal load leaves the last-level cache
+            // to the fields the next launch reads (measured: 0.75% on the Mhat^dag Mhat step)
+            if (A.xnt) SpinorIO<P>::load_nt(A.x + rhs * A.x_stride, A.g.ps, cb, xv);
+            else SpinorIO<P>::load(A.x + rhs * A.x_stride, A.g.ps, cb, xv);
+        }
+        const T a = (T)A.a;
+        // (spelt out: left to the compiler, which product is fused depends on where x was loaded)
+#pragma unroll
+        for (int k = 0; k < 24; ++k) acc[k] = fma(b, acc[k], a * xv[k]);
     } else {
 #pragma unroll
         for (int k = 0; k < 24; ++k) acc[k] *= b;
@@ -301,12 +299,131 @@ __device__ __forceinline__ void dslash_site(const DslashArgs& A, uint32_t cb, co
     }
 }
 
-template <int P, int R, bool DAG, bool XPAY, bool NT, bool PF, int RED = 0>
+template <int P, int R, bool DAG, bool XPAY, bool NT, bool PF, int RED = 0, typename X = HopRaw<P, R>>
+__device__ __forceinline__ void dslash_site(const DslashArgs& A, uint32_t cb, const int c[4], int rhs,
+                                            double* red = nullptr)
+{
+    using T = typename RealOf<P>::T;
+    const size_t gbytes = link_site_bytes(P, R) * (size_t)A.g.ps;
+    const char* in = A.in + rhs * A.in_stride;
+    T acc[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = 0;
+    if constexpr (PF) {
+        X ra, rb;
+        hop_load<0, NT>(A, cb, c, in, gbytes, ra);
+        hop_pipelined<0, DAG, NT>(A, cb, c, in, gbytes, acc, ra, rb);
+        hop_pipelined<1, DAG, NT>(A, cb, c, in, gbytes, acc, rb, ra);
+        hop_pipelined<2, DAG, NT>(A, cb, c, in, gbytes, acc, ra, rb);
+        hop_pipelined<3, DAG, NT>(A, cb, c, in, gbytes, acc, rb, ra);
+        hop_pipelined<4, DAG, NT>(A, cb, c, in, gbytes, acc, ra, rb);
+        hop_pipelined<5, DAG, NT>(A, cb, c, in, gbytes, acc, rb, ra);
+        hop_pipelined<6, DAG, NT>(A, cb, c, in, gbytes, acc, ra, rb);
+        hop_pipelined<7, DAG, NT>(A, cb, c, in, gbytes, acc, rb, ra);
+    } else {
+        hop<0, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<1, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<2, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<3, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<4, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<5, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<6, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+        hop<7, X, DAG, NT>(A, cb, c, in, gbytes, acc);
+    }
+    dslash_finish<P, XPAY, RED, false>(A, cb, rhs, acc, red);
+}
+
+template <int P, int R, bool DAG, bool XPAY, bool NT, bool PF, int RED = 0, typename X = HopRaw<P, R>>
 __device__ __forceinline__ void dslash_site(const DslashArgs& A, uint32_t cb, int rhs, double* red = nullptr)
 {
     int c[4];
     cb_coords(A.g, cb, A.par, c);
-    dslash_site<P, R, DAG, XPAY, NT, PF, RED>(A, cb, c, rhs, red);
+    dslash_site<P, R, DAG, XPAY, NT, PF, RED, X>(A, cb, c, rhs, red);
+}
+
+// The i-th output site in the launch's site order.  The 16-bit kernels join the two orders before
+// the body (90 -> 80 registers in F16); the wide ones keep a body for each (joined, they measured 0.5%
+// slower on the 32^3 x 64 F32 step).
+template <int P, int R, bool DAG, bool XPAY, bool NT, bool PF, int RED = 0>
+__device__ __forceinline__ void dslash_at(const DslashArgs& A, uint32_t i, int rhs, double* red = nullptr)
+{
+    int c[4];
+    if constexpr (P == P_F16 || P == P_BF16) {
+        uint32_t cb = i;
+        if (A.zb > 0) cb = zblock_site(A, i, c);
+        else cb_coords(A.g, i, A.par, c);
+        dslash_site<P, R, DAG, XPAY, NT, PF, RED>(A, cb, c, rhs, red);
+    } else if (A.zb > 0) {
+        const uint32_t cb = zblock_site(A, i, c);
+        dslash_site<P, R, DAG, XPAY, NT, PF, RED>(A, cb, c, rhs, red);
+    } else {
+        dslash_site<P, R, DAG, XPAY, NT, PF, RED>(A, i, rhs, red);
+    }
+}
+
+// A workgroup of four waves covers 64 output sites, wave mu taking the two hops along mu: all of a
+// site's loads are in flight at once instead of two directions of eight, and a lattice of N groups
+// of 64 sites runs 4 N waves.  The half spinors go through LDS and the first wave sums them in the
+// order of dslash_site, so the results are the same bit for bit.  Only the first wave returns true
+// (for sites on the lattice), with the site finished.
+constexpr size_t dslash_split_lds(int P) { return 8 * 12 * 64 * (P == P_F64 ? sizeof(double) : sizeof(float)); }
+
+template <int MU, int P, int R, bool DAG, bool NT>
+__device__ __forceinline__ void split_hops(const DslashArgs& A, uint32_t cb, const int c[4], const char* in,
+                                           float4* lds, int lane)
+{
+    using T = typename RealOf<P>::T;
+    constexpr int NV = 12 * sizeof(T) / 16;   // 16-byte words of a half spinor
+    const size_t gbytes = link_site_bytes(P, R) * (size_t)A.g.ps;
+    HopRaw<P, R> f, b;
+    hop_load<2 * MU, NT>(A, cb, c, in, gbytes, f);
+    hop_load<2 * MU + 1, NT>(A, cb, c, in, gbytes, b);
+    float4 w[NV];
+    hop_half_spinor<2 * MU, DAG>(A, c, f, (T*)w);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) lds[(2 * MU * NV + k) * 64 + lane] = w[k];
+    hop_half_spinor<2 * MU + 1, DAG>(A, c, b, (T*)w);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) lds[((2 * MU + 1) * NV + k) * 64 + lane] = w[k];
+}
+
+template <int D, int P, bool DAG, typename T>
+__device__ __forceinline__ void split_sum(const float4* lds, int lane, T* acc)
+{
+    constexpr int NV = 12 * sizeof(T) / 16;
+    float4 w[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) w[k] = lds[(D * NV + k) * 64 + lane];
+    hop_accumulate<D, DAG>(acc, (const T*)w);
+    if constexpr (D + 1 < 8) split_sum<D + 1, P, DAG>(lds, lane, acc);
+}
+
+template <int P, int R, bool DAG, bool XPAY, bool NT, int RED = 0>
+__device__ __forceinline__ bool dslash_split(const DslashArgs& A, uint32_t group, int rhs, float4* lds,
+                                             double* red = nullptr)
+{
+    using T = typename RealOf<P>::T;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint32_t i = group * 64 + lane;
+    const bool valid = i < (uint32_t)A.g.Vh;
+    const uint32_t cb = valid ? i : 0;   // lanes past the last site work on site 0 and store nothing
+    int c[4];
+    cb_coords(A.g, cb, A.par, c);
+    const char* in = A.in + rhs * A.in_stride;
+    T xv[24];
+    if (XPAY && wave == 0) SpinorIO<P>::load(A.x + rhs * A.x_stride, A.g.ps, cb, xv);
+    if (wave == 0) split_hops<0, P, R, DAG, NT>(A, cb, c, in, lds, lane);
+    else if (wave == 1) split_hops<1, P, R, DAG, NT>(A, cb, c, in, lds, lane);
+    else if (wave == 2) split_hops<2, P, R, DAG, NT>(A, cb, c, in, lds, lane);
+    else split_hops<3, P, R, DAG, NT>(A, cb, c, in, lds, lane);
+    __syncthreads();
+    if (wave != 0 || !valid) return false;
+    T acc[24];
+#pragma unroll
+    for (int k = 0; k < 24; ++k) acc[k] = 0;
+    split_sum<0, P, DAG>(lds, lane, acc);
+    dslash_finish<P, XPAY, RED, XPAY>(A, cb, rhs, acc, red, xv);
+    return true;
 }
 
 } // namespace wd

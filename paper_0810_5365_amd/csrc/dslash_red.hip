@@ -8,22 +8,9 @@
 
 namespace wd {
 
-template <int P, int R, bool DAG, bool NT, bool PF, int RED>
-__global__ void __launch_bounds__(256) dslash_red_kernel(DslashArgs A)
+// The workgroup's sums of each work-item's v[0 .. NV), waves in order.
+template <int NV> __device__ __forceinline__ void red_store(const DslashArgs& A, const double* v)
 {
-    constexpr int NV = red_values(RED);
-    const uint32_t bid = A.remap ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
-    const uint32_t i = bid * blockDim.x + threadIdx.x;
-    double v[3] = {0.0, 0.0, 0.0};
-    if (i < (uint32_t)A.g.Vh) {   // work-items past the last site contribute zeros
-        if (A.zb > 0) {
-            int c[4];
-            const uint32_t cb = zblock_site(A, i, c);
-            dslash_site<P, R, DAG, true, NT, PF, RED>(A, cb, c, 0, v);
-        } else {
-            dslash_site<P, R, DAG, true, NT, PF, RED>(A, i, 0, v);
-        }
-    }
     __shared__ double lds[NV][4];
 #pragma unroll
     for (int n = 0; n < NV; ++n) {
@@ -43,9 +30,44 @@ __global__ void __launch_bounds__(256) dslash_red_kernel(DslashArgs A)
     }
 }
 
+template <int P, int R, bool DAG, bool NT, bool PF, int RED>
+__global__ void __launch_bounds__(256) dslash_red_kernel(DslashArgs A)
+{
+    const uint32_t bid = A.remap ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+    const uint32_t i = bid * blockDim.x + threadIdx.x;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (i < (uint32_t)A.g.Vh)   // work-items past the last site contribute zeros
+        dslash_at<P, R, DAG, true, NT, PF, RED>(A, i, 0, v);
+    red_store<red_values(RED)>(A, v);
+}
+
+// Four waves per 64 sites (dslash_split); the first holds the sites, so its sums are the workgroup's.
+template <int P, int R, bool DAG, bool NT, int RED>
+__global__ void __launch_bounds__(256) dslash_red_split_kernel(DslashArgs A)
+{
+    __shared__ float4 lds[dslash_split_lds(P) / sizeof(float4)];
+    const uint32_t group = A.remap ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+    double v[3] = {0.0, 0.0, 0.0};
+    dslash_split<P, R, DAG, true, NT, RED>(A, group, 0, lds, v);
+    if (threadIdx.x >= 64) return;
+#pragma unroll
+    for (int n = 0; n < red_values(RED); ++n) {
+        double s = v[n];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (threadIdx.x == 0) A.red[(size_t)n * gridDim.x + blockIdx.x] = s;
+    }
+}
+
 template <int P, int R, bool DAG, int RED>
 static wd_status launch_k(wd_context ctx, const DslashArgs& A, const TuneParam& tp, unsigned nblk)
 {
+    if (tp.split) {
+        if (tp.nt) hipLaunchKernelGGL((dslash_red_split_kernel<P, R, DAG, true, RED>), dim3(nblk), dim3(256), 0, ctx->stream, A);
+        else hipLaunchKernelGGL((dslash_red_split_kernel<P, R, DAG, false, RED>), dim3(nblk), dim3(256), 0, ctx->stream, A);
+        WD_LAUNCHED();
+        return WD_OK;
+    }
     const dim3 grid(nblk), block(tp.block);
     switch ((tp.nt ? 1 : 0) | (tp.pf ? 2 : 0)) {
     case 0: hipLaunchKernelGGL((dslash_red_kernel<P, R, DAG, false, false, RED>), grid, block, 0, ctx->stream, A); break;
@@ -97,8 +119,9 @@ wd_status launch_dslash_red(wd_context ctx, const Geom& g, const DslashCall& c, 
         return WD_EINVAL;
     }
     // the launch shape tuned for the same launch without the reduction
-    TuneParam tp = tune_lookup(ctx, dslash_key(g, c));
+    TuneParam tp = dslash_shape(g, c, tune_lookup(ctx, dslash_key(g, c)));
     tp.rhs_inner = 0;
+    if (tp.split) tp.block = 64;   // sites per workgroup
     DslashArgs A;
     WD_TRY(dslash_setup(g, c, tp, &A));
     const unsigned nblk = (unsigned)((g.Vh + tp.block - 1) / tp.block);

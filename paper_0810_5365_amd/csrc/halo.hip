@@ -107,14 +107,14 @@ __global__ void __launch_bounds__(256) dslash_halo_kernel(HaloArgs H)
 #pragma unroll
     for (int k = 0; k < 24; ++k) acc[k] = 0;
     {   // the six spatial directions, each one's loads issued before the previous one's arithmetic
-        T ua[18], pa[24], ub[18], pb[24];
-        hop_load<0, P, R, true>(A, cb, c, A.in, gbytes, ua, pa);
-        hop_pipelined<0, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc, ua, pa, ub, pb);
-        hop_pipelined<1, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc, ub, pb, ua, pa);
-        hop_pipelined<2, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc, ua, pa, ub, pb);
-        hop_pipelined<3, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc, ub, pb, ua, pa);
-        hop_pipelined<4, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc, ua, pa, ub, pb);
-        hop_compute<5, DAG>(A, c, ub, pb, acc);
+        HopRaw<P, R> ra, rb;
+        hop_load<0, true>(A, cb, c, A.in, gbytes, ra);
+        hop_pipelined<0, DAG, true>(A, cb, c, A.in, gbytes, acc, ra, rb);
+        hop_pipelined<1, DAG, true>(A, cb, c, A.in, gbytes, acc, rb, ra);
+        hop_pipelined<2, DAG, true>(A, cb, c, A.in, gbytes, acc, ra, rb);
+        hop_pipelined<3, DAG, true>(A, cb, c, A.in, gbytes, acc, rb, ra);
+        hop_pipelined<4, DAG, true>(A, cb, c, A.in, gbytes, acc, ra, rb);
+        hop_compute<5, DAG>(A, c, rb, acc);
         order_fence(acc);
     }
     const int T_l = A.g.L[3];
@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(256) dslash_halo_kernel(HaloArgs H)
         accumulate<3, S>(acc, w);
         order_fence(acc);
     } else {
-        hop<6, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc);
+        hop<6, HopRaw<P, R>, DAG, true>(A, cb, c, A.in, gbytes, acc);
     }
     if (c[3] == 0) {   // backward t-hop from the previous slab: s_b U_t(x - t)^dagger h, multiplied there
         constexpr int S = DAG ? -1 : 1;
@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(256) dslash_halo_kernel(HaloArgs H)
         for (int k = 0; k < 12; ++k) w[k] *= sg;
         accumulate<3, S>(acc, w);
     } else {
-        hop<7, P, R, DAG, true>(A, cb, c, A.in, gbytes, acc);
+        hop<7, HopRaw<P, R>, DAG, true>(A, cb, c, A.in, gbytes, acc);
     }
     SpinorIO<P>::store(A.out, A.g.ps, cb, acc);
 }

@@ -50,9 +50,9 @@ wd_status tune_save(wd_context ctx, const char* path)
     fprintf(f, "{\"arch\": \"gfx950\", \"entries\": [\n");
     size_t i = 0;
     for (auto& kv : ctx->tune) {
-        fprintf(f, "  {\"key\": \"%s\", \"block\": %d, \"remap\": %d, \"nt\": %d, \"pf\": %d, \"ri\": %d, \"zb\": %d, \"mf\": %d}%s\n",
+        fprintf(f, "  {\"key\": \"%s\", \"block\": %d, \"remap\": %d, \"nt\": %d, \"pf\": %d, \"ri\": %d, \"zb\": %d, \"mf\": %d, \"sp\": %d}%s\n",
                 kv.first.c_str(), kv.second.block, kv.second.remap, kv.second.nt, kv.second.pf, kv.second.rhs_inner,
-                kv.second.zb, kv.second.mf, ++i < ctx->tune.size() ? "," : "");
+                kv.second.zb, kv.second.mf, kv.second.split, ++i < ctx->tune.size() ? "," : "");
     }
     fprintf(f, "]}\n");
     fclose(f);
@@ -77,6 +77,8 @@ wd_status tune_load(wd_context ctx, const char* path)
             if (zb) tp.zb = atoi(zb + 6);
             const char* mf = strstr(p, "\"mf\": ");
             if (mf) tp.mf = atoi(mf + 6);
+            const char* sp = strstr(p, "\"sp\": ");   // absent in a file from before: the shape it tuned
+            tp.split = sp ? atoi(sp + 6) : 0;
             if (tp.block >= 64 && tp.block <= 256 && tp.block % 64 == 0) ctx->tune[key] = tp;
         }
     }
@@ -137,12 +139,23 @@ wd_status autotune_dslash(wd_gauge g, int prec, int nrhs, int* ntuned)
                             tp.pf = pf;
                             tp.rhs_inner = ri;
                             tp.zb = zb;
+                            tp.split = 0;
                             float us;
                             WD_TRY(time_launch(ctx, G, c, tp, reps, &us));
                             cand.emplace_back(us, tp);
                         }
+            {   // four waves per 64 sites: no launch-shape parameters but the remap
+                TuneParam tp;
+                tp.nt = 0;
+                tp.split = 1;
+                float us;
+                WD_TRY(time_launch(ctx, G, c, tp, reps, &us));
+                cand.emplace_back(us, tp);
+            }
             if (mrhs_eligible(c)) {   // the matrix-core path has no launch-shape parameters
                 TuneParam tp;
+                tp.nt = 1;
+                tp.split = 0;
                 tp.mf = 1;
                 float us;
                 WD_TRY(time_launch(ctx, G, c, tp, reps, &us));

@@ -45,11 +45,13 @@ void clear_error();
 struct TuneParam {
     int block = 64;
     int remap = 1;
-    int nt = 1;   // non-temporal link loads
+    int nt = -1;  // non-temporal link loads (-1: by the rule in dslash_shape)
     int pf = 1;   // software-pipelined directions
     int rhs_inner = 1;   // several rhs: interleave them with the site tiles
     int zb = 0;          // z-blocked site traversal depth (0: natural order)
     int mf = 0;          // 16-bit, 12-real, 16k rhs: colour multiply on the matrix cores
+    int split = -1;      // four waves per 64 sites; block, nt, pf, rhs_inner and zb then do not matter
+                         // (-1: by the rule in dslash_shape)
 };
 
 inline bool valid_prec(int p) { return p >= WD_F64 && p <= WD_BF16; }

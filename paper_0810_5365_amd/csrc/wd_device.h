@@ -302,6 +302,8 @@ template <> struct ExtVec<float2> { typedef float T __attribute__((ext_vector_ty
 template <> struct ExtVec<double2> { typedef double T __attribute__((ext_vector_type(2))); };
 template <> struct ExtVec<uint4> { typedef unsigned int T __attribute__((ext_vector_type(4))); };
 template <> struct ExtVec<uint2> { typedef unsigned int T __attribute__((ext_vector_type(2))); };
+template <> struct ExtVec<float> { typedef float T; };
+template <> struct ExtVec<uint32_t> { typedef uint32_t T; };
 
 template <bool NT, typename V> __device__ __forceinline__ V ldv(const V* p)
 {
@@ -322,16 +324,16 @@ template <bool NT> __device__ __forceinline__ uint32_t ldv(const uint32_t* p)
 }
 
 // Element i of a plane whose base is the same for the whole wave: a scalar base and a 32-bit byte
-// offset in one vector register.  The empty constraint keeps the base a scalar pair of its own;
-// left alone, the compiler adds the offset to one plane's base and derives the other planes'
+// offset in one vector register.  readfirstlane keeps the base a scalar pair of its own; left alone, the compiler adds the offset to one plane's base and derives the other planes'
 // addresses from that with 64-bit vector sums, two instructions per load.  Planes stay below 4 GiB:
 // 2^28 sites of 16 bytes, whose canonical links alone (309 GB) exceed the card's memory.
 template <typename V, bool NT = false> __device__ __forceinline__ V ld32(const void* plane, uint32_t i)
 {
     typedef const __attribute__((address_space(1))) char* gptr;
     typedef typename ExtVec<V>::T E;
-    uint64_t p = (uint64_t)plane;
-    asm("" : "+s"(p));
+    const uint64_t a = (uint64_t)plane;
+    const uint64_t p = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) << 32;
     const __attribute__((address_space(1))) E* q =
         (const __attribute__((address_space(1))) E*)((gptr)p + (uint32_t)(i * (uint32_t)sizeof(V)));
     E r;
@@ -414,6 +416,74 @@ template <int P, int R, bool NT> struct LinkIO16 {
 };
 template <int R, bool NT> struct LinkIO<P_F16, R, NT> : LinkIO16<P_F16, R, NT> {};
 template <int R, bool NT> struct LinkIO<P_BF16, R, NT> : LinkIO16<P_BF16, R, NT> {};
+
+// ---------------------------------------------------------------------------
+// What one direction of the hopping term loads, held until it is used.  16-bit fields wait as they
+// come, 13 registers a spinor instead of 24 (the kernel with two directions in flight 80 instead of
+// 99 registers, float16; 32^3 x 64 Mhat^dag Mhat 63.6 us a launch instead of 65.9); the wide types,
+// which have nothing to decode but a link's third row, are held as used (loading them with ld32 and
+// rebuilding the row late measured 1-2% slower at 32^3 x 64).
+// ---------------------------------------------------------------------------
+template <int P, int R> struct HopRaw {
+    uint4 ps[3];
+    float s;
+    uint4 lk[R == 12 ? 1 : 2];
+    uint2 lt;   // 12 reals: codes 8..11; 18 reals: lt.x holds codes 16, 17
+    __device__ __forceinline__ void load_spinor(const char* base, int Vh, uint32_t cb)
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) ps[k] = ld32<uint4>(base + (size_t)k * Vh * 16, cb);
+        s = ld32<float>(base + (size_t)3 * Vh * 16, cb);
+    }
+    template <bool NT> __device__ __forceinline__ void load_link(const char* grp, int Vh, uint32_t cb)
+    {
+        lk[0] = ld32<uint4, NT>(grp, cb);
+        if constexpr (R == 12) {
+            lt = ld32<uint2, NT>(grp + (size_t)Vh * 16, cb);
+        } else {
+            lk[1] = ld32<uint4, NT>(grp + (size_t)Vh * 16, cb);
+            lt.x = ld32<uint32_t, NT>(grp + (size_t)2 * Vh * 16, cb);
+        }
+    }
+    __device__ __forceinline__ void spinor(float* v) const
+    {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) unpack8<P>(ps[k], s, v + 8 * k);
+    }
+    __device__ __forceinline__ void link(float* u) const
+    {
+        unpack8<P>(lk[0], 1.0f, u);
+        if constexpr (R == 12) {
+            u[8] = h2f<P>(lt.x); u[9] = h2f<P>(lt.x >> 16);
+            u[10] = h2f<P>(lt.y); u[11] = h2f<P>(lt.y >> 16);
+            reconstruct_row2(u);
+        } else {
+            unpack8<P>(lk[1], 1.0f, u + 8);
+            u[16] = h2f<P>(lt.x); u[17] = h2f<P>(lt.x >> 16);
+        }
+    }
+};
+template <int P, int R> struct HopRawWide {
+    using T = typename RealOf<P>::T;
+    T u[18], psi[24];
+    __device__ __forceinline__ void load_spinor(const char* base, int Vh, uint32_t cb) { SpinorIO<P>::load(base, Vh, cb, psi); }
+    template <bool NT> __device__ __forceinline__ void load_link(const char* grp, int Vh, uint32_t cb)
+    {
+        LinkIO<P, R, NT>::load(grp, Vh, cb, u);
+    }
+    __device__ __forceinline__ void spinor(T* v) const
+    {
+#pragma unroll
+        for (int k = 0; k < 24; ++k) v[k] = psi[k];
+    }
+    __device__ __forceinline__ void link(T* v) const
+    {
+#pragma unroll
+        for (int k = 0; k < 18; ++k) v[k] = u[k];
+    }
+};
+template <int R> struct HopRaw<P_F32, R> : HopRawWide<P_F32, R> {};
+template <int R> struct HopRaw<P_F64, R> : HopRawWide<P_F64, R> {};
 
 // ---------------------------------------------------------------------------
 // Spin projection (1 + S gamma_mu) in the DeGrand-Rossi basis.

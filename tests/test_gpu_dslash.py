@@ -468,3 +468,66 @@ def test_full_size_even_odd_dslash_32c64(w, ctx):
     ref = orc.d_eo(U, psi_o, BC)
     assert orc.rel_l2(got, ref) < 1e-5
     g.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("dims,recon,nrhs,fixed", [
+    ((2, 2, 2, 2), 12, 1, False),      # eight sites per parity: one partial group
+    ((4, 6, 2, 10), 18, 3, False),     # a remainder group, rhs interleaved
+    ((8, 4, 4, 4), 12, 2, True),       # whole groups, unit t-links
+])
+def test_four_waves_per_group_match_one(w, ctx, monkeypatch, prec, dims, recon, nrhs, fixed):
+    """The dslash with four waves per 64 sites (the untuned choice on small lattices) sums the
+    directions in the plain kernel's order: bit-identical, plain and fused, with and without the
+    dagger, with kept and with streamed links."""
+    import torch
+    p = w.PREC_BY_NAME[prec]
+    X, Y, Z, T = dims
+    g = w.Gauge(ctx, dims, BC, recon)
+    g.upload(ls.gauge_field(dims, 0.5, 901))
+    if fixed:
+        w.wd_gauge_fix_temporal(g.handle, None)
+    lat = w.lattice(dims, BC)
+    psi = ls.gaussian_complex((nrhs, X * Y * Z * T // 2, 4, 3), 902, ls.STREAM_SPINOR)
+    fin = w.pack(ctx, lat, w.ODD, p, psi, nrhs)
+    fx = w.pack(ctx, lat, w.EVEN, p, psi[::-1].copy(), nrhs)
+    for dag in (0, 1):
+        for xpay in (False, True):
+            outs = []
+            for split, nt in (("0", "0"), ("1", "0"), ("1", "1")):
+                monkeypatch.setenv("WD_DSLASH_SPLIT", split)
+                monkeypatch.setenv("WD_DSLASH_NT", nt)
+                out = torch.zeros_like(fx)
+                if xpay:
+                    w.wd_dslash_xpay(g.handle, w.EVEN, dag, p, nrhs, fin.data_ptr(), fx.data_ptr(), 1.0, -0.015, out.data_ptr())
+                else:
+                    w.wd_dslash(g.handle, w.EVEN, dag, p, nrhs, fin.data_ptr(), out.data_ptr())
+                torch.cuda.synchronize()
+                outs.append(out)
+            assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (dag, xpay)
+    g.close()
+
+
+@pytest.mark.parametrize("sloppy", ["f64", "f32", "f16"])
+def test_four_waves_per_group_sum_the_same_reductions(w, ctx, monkeypatch, sloppy):
+    """CG and BiCGstab, whose inner products the dslash launches sum, return the same bits with
+    either kernel (4x6x4x10: a remainder group)."""
+    import ctypes
+    import torch
+    dims = (4, 6, 4, 10)
+    X, Y, Z, T = dims
+    g = w.Gauge(ctx, dims, BC, 12)
+    g.upload(ls.gauge_field(dims, 0.6, 903))
+    lat = w.lattice(dims, BC)
+    b = w.pack(ctx, lat, w.FULL, w.F64, ls.gaussian_complex((T, Z, Y, X, 4, 3), 904, ls.STREAM_SPINOR))
+    prm = w.solver_params(tol=1e-10, maxiter=500, sloppy=w.PREC_BY_NAME[sloppy])
+    for solve in (w.wd_wilson_solve, w.wd_bicgstab_solve):
+        xs = []
+        for split in ("0", "1"):
+            monkeypatch.setenv("WD_DSLASH_SPLIT", split)
+            x = torch.zeros_like(b)
+            info = w.WdSolverInfo()
+            solve(g.handle, 0.124, ctypes.byref(prm), b.data_ptr(), x.data_ptr(), ctypes.byref(info))
+            xs.append(x)
+        assert torch.equal(xs[0], xs[1])
+    g.close()
