@@ -77,13 +77,22 @@ wd_status launch_pack_gauge(wd_context ctx, const Geom& g, int prec, int recon, 
 // ---- spinors ---------------------------------------------------------------
 // One work-item per (rhs, site).  FULL: canonical lexicographic site order;
 // EVEN / ODD: canonical checkerboard order of that parity.
+// Unpacking goes through LDS: a site's 192 canonical bytes stored by its own work-item spread every
+// store instruction over 64 lines.  32^3 x 64 FULL F64 (806 MB): 130 us, 196 us before (6.2 TB/s, part
+// of the field in the last-level cache).  Packing reads them that way at the copy rate already
+// (152 us; through LDS 172 us, with fewer waves on a CU).
+constexpr int PACK_BLOCK = 256;
+
 template <int P, bool UNPACK>
-__global__ void spinor_pack_kernel(double* __restrict__ canon, char* __restrict__ packed, Geom g, int subset,
-                                   long long nsites_per_rhs, long long ntotal)
+__global__ void __launch_bounds__(PACK_BLOCK) spinor_pack_kernel(double* __restrict__ canon, char* __restrict__ packed,
+                                                                 Geom g, int subset, long long nsites_per_rhs,
+                                                                 long long ntotal)
 {
     using T = typename RealOf<P>::T;
-    const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ntotal) return;
+    const long long i0 = (long long)blockIdx.x * PACK_BLOCK + threadIdx.x;
+    const bool live = i0 < ntotal;
+    if (!UNPACK && !live) return;
+    const long long k = live ? i0 : 0;   // (work-items past the end of an unpack work on site 0 and store nothing)
     const long long rhs = k / nsites_per_rhs;
     const long long s = k - rhs * nsites_per_rhs;
     const size_t hb = spinor_site_bytes(P) * (size_t)g.ps;
@@ -103,12 +112,26 @@ __global__ void spinor_pack_kernel(double* __restrict__ canon, char* __restrict_
         cb = (uint32_t)s;
         base = packed + (size_t)rhs * hb;
     }
-    double* c = canon + 24 * k;
     T v[24];
     if constexpr (UNPACK) {
+        constexpr int ROW = 26;   // doubles per staged site: 24 + 2 of padding (conflict-free 16-byte access)
+        __shared__ __attribute__((aligned(16))) double lds[PACK_BLOCK * ROW];
+        const int lane = threadIdx.x & 63;
+        double* rows = lds + (threadIdx.x - lane) * ROW;
         SpinorIO<P>::load(base, g.ps, cb, v);
-        for (int i = 0; i < 24; ++i) c[i] = (double)v[i];
+#pragma unroll
+        for (int i = 0; i < 12; ++i)
+            *(double2*)&rows[lane * ROW + 2 * i] = make_double2((double)v[2 * i], (double)v[2 * i + 1]);
+        __syncthreads();
+        // the wave's 64 sites are 12 KB in a row: each store instruction writes 1 KB of them
+        const long long k0 = i0 - lane;
+#pragma unroll
+        for (int i = 0; i < 12; ++i) {
+            const int e = lane + 64 * i, site = e / 12, part = e - 12 * site;
+            if (k0 + site < ntotal) *(double2*)(canon + 24 * (k0 + site) + 2 * part) = *(const double2*)&rows[site * ROW + 2 * part];
+        }
     } else {
+        const double* c = canon + 24 * k;
         for (int i = 0; i < 24; ++i) v[i] = (T)c[i];
         SpinorIO<P>::store(base, g.ps, cb, v);
     }
@@ -120,7 +143,7 @@ static wd_status spinor_pack_t(wd_context ctx, const Geom& g, int subset, int nr
 {
     const long long per = subset == WD_FULL ? 2ll * g.Vh : (long long)g.Vh;
     const long long n = per * nrhs;
-    const int bs = 256;
+    const int bs = PACK_BLOCK;
     const dim3 grid((unsigned)((n + bs - 1) / bs));
     if (unpack)
         hipLaunchKernelGGL((spinor_pack_kernel<P, true>), grid, dim3(bs), 0, ctx->stream, (double*)canon,

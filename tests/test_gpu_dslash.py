@@ -531,3 +531,28 @@ def test_four_waves_per_group_sum_the_same_reductions(w, ctx, monkeypatch, slopp
             xs.append(x)
         assert torch.equal(xs[0], xs[1])
     g.close()
+
+@pytest.mark.parametrize("dims,subset,nrhs", [
+    ((2, 2, 2, 2), "even", 1),     # eight sites: part of one wave
+    ((2, 2, 2, 2), "full", 4),     # one wave exactly, rhs boundaries inside it
+    ((4, 6, 2, 10), "full", 1),    # 480 sites: a remainder workgroup and wave
+    ((4, 6, 2, 10), "odd", 3),
+])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_pack_and_unpack_edges(w, ctx, dims, subset, nrhs, prec):
+    """Unpacking stages a wave's canonical sites in LDS: at the edges of waves and workgroups the
+    round trip is exact (float32: the rounded values), and nothing past the field is written."""
+    import torch
+    X, Y, Z, T = dims
+    sub, p = w.SUBSET_BY_NAME[subset], w.PREC_BY_NAME[prec]
+    n = X * Y * Z * T // (1 if subset == "full" else 2)
+    lat = w.lattice(dims, BC)
+    src = torch.from_numpy(ls.gaussian_complex((nrhs, n, 4, 3), 905, ls.STREAM_SPINOR).view(np.float64)).cuda().reshape(-1)
+    packed = w.pack(ctx, lat, sub, p, src, nrhs)
+    back = torch.full((src.numel() + 64,), float("nan"), dtype=torch.float64, device="cuda")
+    import ctypes
+    w.wd_spinor_unpack(ctx.handle, ctypes.byref(lat), sub, p, nrhs, packed.data_ptr(), back.data_ptr())
+    torch.cuda.synchronize()
+    want = src if prec == "f64" else src.float().double()
+    assert torch.equal(back[:src.numel()], want)
+    assert torch.isnan(back[src.numel():]).all()
