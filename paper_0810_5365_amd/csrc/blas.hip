@@ -56,6 +56,35 @@ template <int N> __device__ __forceinline__ void block_reduce(double* v, double*
     }
 }
 
+// The same for N = 8, 16 or 32 values, halving the values a lane holds with each exchange: N - 1
+// exchanges down to one value per lane and log2(64 / N) more, instead of 6 N.
+template <int N> __device__ __forceinline__ void block_reduce_many(const double* v, double* partials)
+{
+    constexpr int LOG = N == 8 ? 3 : N == 16 ? 4 : 5;
+    __shared__ double lds[N][RED_BLOCK / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double a[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) a[n] = v[n];
+#pragma unroll
+    for (int step = 0; step < LOG; ++step) {   // lanes with bit 5 - step set keep the upper half
+        const int off = 32 >> step, half = N >> (step + 1);
+        const bool upper = lane & off;
+#pragma unroll
+        for (int n = 0; n < half; ++n) {
+            const double send = upper ? a[n] : a[n + half];
+            a[n] = (upper ? a[n + half] : a[n]) + __shfl_xor(send, off, 64);
+        }
+    }
+#pragma unroll
+    for (int off = 32 >> LOG; off > 0; off >>= 1) a[0] += __shfl_xor(a[0], off, 64);
+    if ((lane & ((64 >> LOG) - 1)) == 0) lds[lane >> (6 - LOG)][wave] = a[0];
+    __syncthreads();
+    if (threadIdx.x < N)
+        partials[(size_t)threadIdx.x * gridDim.x + blockIdx.x] =
+            ((lds[threadIdx.x][0] + lds[threadIdx.x][1]) + lds[threadIdx.x][2]) + lds[threadIdx.x][3];
+}
+
 // This thread's share of the sum of p[0 .. n) over a RED_BLOCK workgroup, in a fixed order:
 // four accumulators, so that four loads are in flight per thread instead of one at a time.
 __device__ __forceinline__ double thread_share(const double* __restrict__ p, int n)
@@ -648,45 +677,40 @@ wd_status blas_lincomb(wd_context ctx, const Geom& g, size_t nh, int prec, int n
 }
 
 // ---- block Gram-Schmidt helpers (flexible GMRES) ---------------------------------------
-// <V_i, w> for i < k, and (with_norm) ||w||^2 as value k.  Vectors go in groups of four:
-// w is read once per group, so a pass reads k + ceil((k + 1) / 4) fields instead of 2 (k + 1).
+// <V_i, w> for i < k, and (with_norm) ||w||^2 as value k.  Vectors go in groups of four, a workgroup
+// (grid y) each: w is read once per group, and the five sites' loads of a work-item are in flight
+// together (entries past the last are w again, their sums not looked at).  16^3 x 32 has one wave per
+// SIMD and group, so the kernel is bound by its loads' and its sums' latency: one to five vectors 5.0-9 us,
+// 6.7-12 us before.
 constexpr int MDOT_GROUP = 4;
 
 template <int P>
-__global__ void __launch_bounds__(RED_BLOCK) mdot_kernel(SiteRange Vs, size_t vstride, int k, int with_norm, SiteRange W,
-                                                         long long nsites, double* partials)
+__global__ void __launch_bounds__(RED_BLOCK) mdot_kernel(SiteRange Vs, size_t vstride, int k, SiteRange W, long long nsites,
+                                                         double* partials)
 {
-    const int n = k + (with_norm ? 1 : 0);
-    for (int i0 = 0; i0 < n; i0 += MDOT_GROUP) {
-        double acc[2 * MDOT_GROUP];
+    using T = typename RealOf<P>::T;
+    const int i0 = blockIdx.y * MDOT_GROUP;
+    double acc[2 * MDOT_GROUP];
 #pragma unroll
-        for (int q = 0; q < 2 * MDOT_GROUP; ++q) acc[q] = 0.0;
-        for (long long s = (long long)blockIdx.x * RED_BLOCK + threadIdx.x; s < nsites; s += (long long)gridDim.x * RED_BLOCK) {
-            const long long h = s / W.Vh;
-            const uint32_t cb = (uint32_t)(s - h * W.Vh);
-            typename RealOf<P>::T b[24];
-            SpinorIO<P>::load(W.half(h), W.ps, cb, b);
+    for (int q = 0; q < 2 * MDOT_GROUP; ++q) acc[q] = 0.0;
+    for (long long s = (long long)blockIdx.x * RED_BLOCK + threadIdx.x; s < nsites; s += (long long)gridDim.x * RED_BLOCK) {
+        const long long h = s / W.Vh;
+        const uint32_t cb = (uint32_t)(s - h * W.Vh);
+        T b[24], a[MDOT_GROUP][24];
+        SpinorIO<P>::load(W.half(h), W.ps, cb, b);
 #pragma unroll
-            for (int u = 0; u < MDOT_GROUP; ++u) {
-                const int i = i0 + u;
-                if (i >= n) break;
-                typename RealOf<P>::T a[24];
-                if (i < k) SpinorIO<P>::load(Vs.half(h) + (size_t)i * vstride, W.ps, cb, a);
-                else {
+        for (int u = 0; u < MDOT_GROUP; ++u)
+            SpinorIO<P>::load(i0 + u < k ? Vs.half(h) + (size_t)(i0 + u) * vstride : W.half(h), W.ps, cb, a[u]);
 #pragma unroll
-                    for (int q = 0; q < 24; ++q) a[q] = b[q];
-                }
+        for (int u = 0; u < MDOT_GROUP; ++u)
 #pragma unroll
-                for (int q = 0; q < 12; ++q) {
-                    const double ar = a[2 * q], ai = a[2 * q + 1], br = b[2 * q], bi = b[2 * q + 1];
-                    acc[2 * u] += ar * br + ai * bi;
-                    acc[2 * u + 1] += ar * bi - ai * br;
-                }
+            for (int q = 0; q < 12; ++q) {
+                const double ar = a[u][2 * q], ai = a[u][2 * q + 1], br = b[2 * q], bi = b[2 * q + 1];
+                acc[2 * u] += ar * br + ai * bi;
+                acc[2 * u + 1] += ar * bi - ai * br;
             }
-        }
-        block_reduce<2 * MDOT_GROUP>(acc, partials + (size_t)2 * i0 * gridDim.x);
-        __syncthreads();
     }
+    block_reduce_many<2 * MDOT_GROUP>(acc, partials + (size_t)2 * i0 * gridDim.x);
 }
 
 wd_status blas_mdot(wd_context ctx, const Geom& g, size_t nh, int prec, const void* V, size_t vstride, int k,
@@ -703,8 +727,8 @@ wd_status blas_mdot(wd_context ctx, const Geom& g, size_t nh, int prec, const vo
     WD_TRY(ensure_reduction(ctx, (size_t)nblk * 2 * MDOT_GROUP * ngrp));
     SiteRange Vs{(const char*)V, g.Vh, g.ps, half_bytes(g, prec)}, W{(const char*)w, g.Vh, g.ps, half_bytes(g, prec)};
     switch (prec) {
-    case WD_F64: hipLaunchKernelGGL(mdot_kernel<P_F64>, dim3(nblk), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, (int)with_norm, W, ns, ctx->partials); break;
-    case WD_F32: hipLaunchKernelGGL(mdot_kernel<P_F32>, dim3(nblk), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, (int)with_norm, W, ns, ctx->partials); break;
+    case WD_F64: hipLaunchKernelGGL(mdot_kernel<P_F64>, dim3(nblk, ngrp), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, W, ns, ctx->partials); break;
+    case WD_F32: hipLaunchKernelGGL(mdot_kernel<P_F32>, dim3(nblk, ngrp), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, W, ns, ctx->partials); break;
     default: set_error("mdot: precision %d not supported", prec); return WD_EUNSUPPORTED;
     }
     WD_LAUNCHED();
@@ -718,13 +742,14 @@ struct MaxpyCoef {
 // out = scale * (w + sum_i c_i V_i); out may be w.  With dcoef non-null the coefficients are
 // c_i = dsign * (dcoef[2i], dcoef[2i + 1]), read from device memory (a previous reduction).
 template <int P>
-__global__ void maxpy_kernel(SiteRange Vs, size_t vstride, int nvec, MaxpyCoef cf, const double* dcoef, float dsign,
+__global__ void __launch_bounds__(256) maxpy_kernel(SiteRange Vs, size_t vstride, int nvec, MaxpyCoef cf, const double* dcoef, float dsign,
                              float scale, SiteRange W, SiteRange O, long long n)
 {
     WD_SITE_LOOP(n, W.Vh)
     using T = typename RealOf<P>::T;
     T w[24];
     SpinorIO<P>::load(W.half(h), W.ps, cb, w);
+#pragma unroll 4
     for (int i = 0; i < nvec; ++i) {
         T v[24];
         SpinorIO<P>::load(Vs.half(h) + (size_t)i * vstride, W.ps, cb, v);
@@ -769,71 +794,100 @@ wd_status blas_maxpy(wd_context ctx, const Geom& g, size_t nh, int prec, const v
 
 // Second Gram-Schmidt pass fused with the first pass's update: per site
 //   w' = w - sum_i h1_i V_i   (h1 from dres[slot1 ..], written back to w)
-//   partial <V_i, w'> for i < k and ||w'||^2, with V_i read once from HBM (the dots re-read
-//   the site's V_i from cache right after the update).  Up to MGS_KMAX vectors; the norm
-//   lands in value 2 MGS_KMAX.
-
-template <int P>
+//   partial <V_i, w'> for i < k and ||w'||^2 (value 2 KM), with V_i read once from HBM.
+// KM = 4, 8 or 16, the smallest that holds k: the 2 KM + 1 sums are most of the kernel on a small
+// lattice, and up to four vectors stay in registers between the two uses (eight spill; beyond four
+// the dots read them again from cache).  16^3 x 32, one to four vectors 8.4 us, five 16 us; before,
+// with 33 sums of six exchanges each whatever k, 15-18 us.
+template <int P, int KM>
 __global__ void __launch_bounds__(RED_BLOCK) maxpy_mdot_kernel(SiteRange Vs, size_t vstride, int k, const double* h1,
                                                                SiteRange W, long long nsites, double* partials)
 {
     using T = typename RealOf<P>::T;
-    double acc[2 * MGS_KMAX + 1];
+    constexpr bool KEEP = KM <= 4;
+    double acc[2 * KM], nn[1] = {0.0};
 #pragma unroll
-    for (int q = 0; q < 2 * MGS_KMAX + 1; ++q) acc[q] = 0.0;
+    for (int q = 0; q < 2 * KM; ++q) acc[q] = 0.0;
+    auto update = [&](T* w, const T* v, int i) {
+        const T cr = (T)(-(float)h1[2 * i]), ci = (T)(-(float)h1[2 * i + 1]);
+#pragma unroll
+        for (int q = 0; q < 12; ++q) {
+            w[2 * q] += cr * v[2 * q] - ci * v[2 * q + 1];
+            w[2 * q + 1] += cr * v[2 * q + 1] + ci * v[2 * q];
+        }
+    };
+    auto dot = [&](const T* w, const T* v, int i) {
+#pragma unroll
+        for (int q = 0; q < 12; ++q) {
+            const double ar = v[2 * q], ai = v[2 * q + 1], br = w[2 * q], bi = w[2 * q + 1];
+            acc[2 * i] += ar * br + ai * bi;
+            acc[2 * i + 1] += ar * bi - ai * br;
+        }
+    };
     for (long long s = (long long)blockIdx.x * RED_BLOCK + threadIdx.x; s < nsites; s += (long long)gridDim.x * RED_BLOCK) {
         const long long h = s / W.Vh;
         const uint32_t cb = (uint32_t)(s - h * W.Vh);
         T w[24];
         SpinorIO<P>::load(W.half(h), W.ps, cb, w);
-        for (int i = 0; i < k; ++i) {
-            T v[24];
-            SpinorIO<P>::load(Vs.half(h) + (size_t)i * vstride, W.ps, cb, v);
-            const T cr = (T)(-(float)h1[2 * i]), ci = (T)(-(float)h1[2 * i + 1]);
+        if constexpr (KEEP) {
+            T v[KM][24];
 #pragma unroll
-            for (int q = 0; q < 12; ++q) {
-                w[2 * q] += cr * v[2 * q] - ci * v[2 * q + 1];
-                w[2 * q + 1] += cr * v[2 * q + 1] + ci * v[2 * q];
-            }
-        }
-        SpinorIO<P>::store((char*)W.half(h), W.ps, cb, w);
+            for (int i = 0; i < KM; ++i)   // (entries past k repeat the last vector and are not used)
+                SpinorIO<P>::load(Vs.half(h) + (size_t)(i < k ? i : k - 1) * vstride, W.ps, cb, v[i]);
 #pragma unroll
-        for (int i = 0; i < MGS_KMAX; ++i) {
-            if (i < k) {
+            for (int i = 0; i < KM; ++i)
+                if (i < k) update(w, v[i], i);
+            SpinorIO<P>::store((char*)W.half(h), W.ps, cb, w);
+#pragma unroll
+            for (int i = 0; i < KM; ++i) dot(w, v[i], i);
+        } else {
+#pragma unroll 4
+            for (int i = 0; i < k; ++i) {
                 T v[24];
                 SpinorIO<P>::load(Vs.half(h) + (size_t)i * vstride, W.ps, cb, v);
+                update(w, v, i);
+            }
+            SpinorIO<P>::store((char*)W.half(h), W.ps, cb, w);
 #pragma unroll
-                for (int q = 0; q < 12; ++q) {
-                    const double ar = v[2 * q], ai = v[2 * q + 1], br = w[2 * q], bi = w[2 * q + 1];
-                    acc[2 * i] += ar * br + ai * bi;
-                    acc[2 * i + 1] += ar * bi - ai * br;
+            for (int i = 0; i < KM; ++i) {
+                if (i < k) {
+                    T v[24];
+                    SpinorIO<P>::load(Vs.half(h) + (size_t)i * vstride, W.ps, cb, v);
+                    dot(w, v, i);
                 }
             }
         }
 #pragma unroll
-        for (int q = 0; q < 24; ++q) acc[2 * MGS_KMAX] += (double)w[q] * (double)w[q];
+        for (int q = 0; q < 24; ++q) nn[0] += (double)w[q] * (double)w[q];
     }
-    block_reduce<2 * MGS_KMAX + 1>(acc, partials);
+    block_reduce_many<2 * KM>(acc, partials);
+    block_reduce<1>(nn, partials + (size_t)2 * KM * gridDim.x);
 }
 
 wd_status blas_maxpy_mdot(wd_context ctx, const Geom& g, size_t nh, int prec, const void* V, size_t vstride, int k,
-                          int slot1, void* w)
+                          int slot1, void* w, int* norm_at)
 {
     if (k < 1 || k > MGS_KMAX || slot1 < 2 * MGS_KMAX + 1 || slot1 + 2 * k > 256) {
         set_error("maxpy_mdot: k = %d (slot %d) out of range", k, slot1);
         return WD_EINVAL;
     }
+    if (prec != WD_F32) {
+        set_error("maxpy_mdot: precision %d not supported (F32 only)", prec);
+        return WD_EUNSUPPORTED;
+    }
     const long long ns = (long long)nh * g.Vh;
     const int nblk = red_blocks(ns);
-    WD_TRY(ensure_reduction(ctx, (size_t)nblk * (2 * MGS_KMAX + 1)));
+    const int km = k <= 4 ? 4 : (k <= 8 ? 8 : 16);
+    static_assert(MGS_KMAX == 16, "the kernel is built for 4, 8 and 16 vectors");
+    WD_TRY(ensure_reduction(ctx, (size_t)nblk * (2 * km + 1)));
     SiteRange Vs{(const char*)V, g.Vh, g.ps, half_bytes(g, prec)}, W{(const char*)w, g.Vh, g.ps, half_bytes(g, prec)};
-    switch (prec) {
-    case WD_F32: hipLaunchKernelGGL(maxpy_mdot_kernel<P_F32>, dim3(nblk), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k,
-                                    (const double*)(ctx->dres + slot1), W, ns, ctx->partials); break;
-    default: set_error("maxpy_mdot: precision %d not supported (F32 only)", prec); return WD_EUNSUPPORTED;
-    }
+    const double* h1 = ctx->dres + slot1;
+    if (km == 4) hipLaunchKernelGGL((maxpy_mdot_kernel<P_F32, 4>), dim3(nblk), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, h1, W, ns, ctx->partials);
+    else if (km == 8) hipLaunchKernelGGL((maxpy_mdot_kernel<P_F32, 8>), dim3(nblk), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, h1, W, ns, ctx->partials);
+    else hipLaunchKernelGGL((maxpy_mdot_kernel<P_F32, 16>), dim3(nblk), dim3(RED_BLOCK), 0, ctx->stream, Vs, vstride, k, h1, W, ns, ctx->partials);
     WD_LAUNCHED();
-    return finish(ctx, nblk, 2 * MGS_KMAX + 1, true);
+    *norm_at = 2 * km;
+    return finish(ctx, nblk, 2 * km + 1, true);
 }
 
 wd_status blas_maxpy_dev(wd_context ctx, const Geom& g, size_t nh, int prec, const void* V, size_t vstride, int k,

@@ -184,8 +184,7 @@ static wd_status fgmres_run(wd_gauge g, double kappa, const wd_solver_params& pr
             int norm_at = 2 * (j + 1);
             if (j + 1 <= MGS_KMAX) {
                 // the first pass's update and the second pass's dots in one sweep over V
-                WD_TRY(blas_maxpy_mdot(ctx, G, nh, WD_F32, V, v32, j + 1, SLOT_H1, wv));
-                norm_at = 2 * MGS_KMAX;
+                WD_TRY(blas_maxpy_mdot(ctx, G, nh, WD_F32, V, v32, j + 1, SLOT_H1, wv, &norm_at));
             } else {
                 WD_TRY(blas_maxpy_dev(ctx, G, nh, WD_F32, V, v32, j + 1, SLOT_H1, -1.0f, wv, 1.0, wv));
                 WD_TRY(blas_mdot(ctx, G, nh, WD_F32, V, v32, j + 1, wv, true, true));

@@ -220,3 +220,30 @@ def test_trained_network_cuts_iterations_on_unseen_fields():
         assert its["net"] <= 0.75 * its["plain"], its
         g.close()
     ctx.close()
+
+@pytest.mark.parametrize("restart", [3, 4, 5, 8, 9, 20])
+def test_gram_schmidt_kernel_widths(restart):
+    """Flexible GMRES with cycles ending at the edges of its fused Gram-Schmidt kernels (4, 8 and 16
+    vectors, and past 16 the separate passes): the oracle's residual meets the tolerance, and with a
+    loose cycle reduction every width up to the restart length is used."""
+    import ctypes
+    import torch
+    from paper_0810_5365_amd import wdirac as w
+    dims, kappa, tol = (4, 6, 4, 10), 0.1248, 1e-10
+    X, Y, Z, T = dims
+    ctx = w.Context(0)
+    U = ls.gauge_field(dims, 0.7, 7101)
+    g = w.Gauge(ctx, dims, (1, 1, 1, -1), 12)
+    g.upload(U)
+    lat = w.lattice(dims, (1, 1, 1, -1))
+    b = ls.gaussian_complex((T, Z, Y, X, 4, 3), 7102, ls.STREAM_SPINOR)
+    fb = w.pack(ctx, lat, w.FULL, w.F64, b)
+    fx = torch.zeros_like(fb)
+    prm = w.solver_params(tol=tol, maxiter=400, sloppy=w.F32, delta=1e-8)
+    info = w.WdSolverInfo()
+    w.wd_fgmres_solve(g.handle, kappa, ctypes.byref(prm), restart, 0, None, None, w.F32, fb.data_ptr(), fx.data_ptr(),
+                      ctypes.byref(info))
+    x = w.unpack(ctx, lat, w.FULL, w.F64, fx, b.shape)
+    assert orc.rel_residual(lambda v: orc.apply_m(U, v, kappa, (1, 1, 1, -1)), x, b) <= 1.05 * tol
+    g.close()
+    ctx.close()
