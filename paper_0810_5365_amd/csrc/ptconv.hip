@@ -344,6 +344,21 @@ constexpr int WG_LD = 20;      // floats per staged row: 16 columns + 4 of paddi
 constexpr int WG_WAVES = 8;    // waves per workgroup
 constexpr int wg_units(int tc) { return (9 * tc + 7) / 8; }   // products of all nine paths
 
+// ld32 where the compiler already knows the base to be the wave's own (no divergent branch around
+// the loads): an empty constraint instead of readfirstlane, which costs this kernel registers.
+template <typename V> __device__ __forceinline__ V wg_ld(const void* plane, uint32_t i)
+{
+    typedef typename ExtVec<V>::T E;
+    uint64_t p = (uint64_t)plane;
+    asm("" : "+s"(p));
+    const E r = *(const __attribute__((address_space(1))) E*)((const __attribute__((address_space(1))) char*)p +
+                                                               (uint32_t)(i * (uint32_t)sizeof(V)));
+    V v;
+    static_assert(sizeof(v) == sizeof(r), "vector size");
+    __builtin_memcpy(&v, &r, sizeof(v));
+    return v;
+}
+
 // Neighbour features (and the link) of one path as loaded.
 template <int R, int TC> struct WgRaw {
     float4 l[R == 12 ? 3 : 4];
@@ -387,8 +402,8 @@ __device__ __forceinline__ void wg_load(const WgArgs& A, int path, const float2*
         const uint32_t ls = fwd ? cb : nb;
         const char* grp = A.gauge + (size_t)(2 * mu + lpar) * link_site_bytes(P_F32, R) * A.g.ps;
 #pragma unroll
-        for (int k = 0; k < (R == 12 ? 3 : 4); ++k) x.l[k] = ld32<float4>(grp + (size_t)k * A.g.ps * 16, ls);
-        if constexpr (R == 18) x.l18 = ld32<float2>(grp + (size_t)4 * A.g.ps * 16, ls);
+        for (int k = 0; k < (R == 12 ? 3 : 4); ++k) x.l[k] = wg_ld<float4>(grp + (size_t)k * A.g.ps * 16, ls);
+        if constexpr (R == 18) x.l18 = wg_ld<float2>(grp + (size_t)4 * A.g.ps * 16, ls);
         src = nb;
         spar = 1 - par;
     }
@@ -397,7 +412,7 @@ __device__ __forceinline__ void wg_load(const WgArgs& A, int path, const float2*
     for (int b = 0; b < TC; ++b)
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-            x.v[b][k] = ld32<float2>(site + (size_t)((b < A.ctr ? b : A.ctr - 1) * 6 + k) * Vh, src);
+            x.v[b][k] = wg_ld<float2>(site + (size_t)((b < A.ctr ? b : A.ctr - 1) * 6 + k) * Vh, src);
 }
 
 // T_p of the loaded features into the wave's staging rows (colour, site), columns col0 ..
@@ -510,7 +525,7 @@ __device__ __forceinline__ void wg_run(const WgArgs& A, int u0, float* lds)
             for (int b = 0; b < 8; ++b)
 #pragma unroll
                 for (int k = 0; k < 3; ++k)
-                    v[b][k] = ld32<float2>(site + (size_t)((b < A.craw ? b : A.craw - 1) * 6 + k) * Vh, cb);
+                    v[b][k] = wg_ld<float2>(site + (size_t)((b < A.craw ? b : A.craw - 1) * 6 + k) * Vh, cb);
 #pragma unroll
             for (int k = 0; k < 3; ++k)
 #pragma unroll
