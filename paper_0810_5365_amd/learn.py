@@ -20,6 +20,7 @@ Everything numeric runs in the library's HIP kernels; this module only
 marshals tensors and drives the loop.
 """
 import ctypes
+import math
 import time
 
 import numpy as np
@@ -102,10 +103,12 @@ def make_pairs(field, kappa, psi, n):
 
 
 def sample_norms(v, n):
-    """||v_i||^2 of n samples of 4-channel features.  In two steps: a sum over whole samples gives the
-    device n rows to work on (8 on 16^3 x 32: 406 us, one workgroup a row), 384 a sample fill it
-    (25 us); 48 reals per pair of sites and at least eight pairs always divide so."""
-    return v.view(n, 384, -1).sum(2).sum(1)
+    """The n samples' sums of v (squares already).  In two steps: a sum over whole samples gives the device n rows to work on
+    (8 on 16^3 x 32: 406 us, one workgroup a row), 384 a sample fill it (25 us).  Four channels on any
+    lattice divide into 384 rows (48 reals per pair of sites, at least eight pairs); fewer channels
+    on the smallest lattices into the largest number of rows that does."""
+    rows = math.gcd(v.numel() // n, 384)
+    return v.view(n, rows, -1).sum(2).sum(1)
 
 
 def batch_loss(net, field, x, t, n):
