@@ -80,10 +80,11 @@ wd_status launch_pack_gauge(wd_context ctx, const Geom& g, int prec, int recon, 
 // Unpacking goes through LDS: a site's 192 canonical bytes stored by its own work-item spread every
 // store instruction over 64 lines.  32^3 x 64 FULL F64 (806 MB): 130 us, 196 us before (6.2 TB/s, part
 // of the field in the last-level cache).  Packing reads them that way at the copy rate already
-// (152 us; through LDS 172 us, with fewer waves on a CU).
+// (152 us; through LDS 172 us, with fewer waves on a CU).  The canonical field is an array of doubles
+// and need not be aligned to more than one: ALIGNED says that it is to 16 bytes, and stores pairs.
 constexpr int PACK_BLOCK = 256;
 
-template <int P, bool UNPACK>
+template <int P, bool UNPACK, bool ALIGNED = true>
 __global__ void __launch_bounds__(PACK_BLOCK) spinor_pack_kernel(double* __restrict__ canon, char* __restrict__ packed,
                                                                  Geom g, int subset, long long nsites_per_rhs,
                                                                  long long ntotal)
@@ -125,10 +126,18 @@ __global__ void __launch_bounds__(PACK_BLOCK) spinor_pack_kernel(double* __restr
         __syncthreads();
         // the wave's 64 sites are 12 KB in a row: each store instruction writes 1 KB of them
         const long long k0 = i0 - lane;
+        if constexpr (ALIGNED) {
 #pragma unroll
-        for (int i = 0; i < 12; ++i) {
-            const int e = lane + 64 * i, site = e / 12, part = e - 12 * site;
-            if (k0 + site < ntotal) *(double2*)(canon + 24 * (k0 + site) + 2 * part) = *(const double2*)&rows[site * ROW + 2 * part];
+            for (int i = 0; i < 12; ++i) {
+                const int e = lane + 64 * i, site = e / 12, part = e - 12 * site;
+                if (k0 + site < ntotal) *(double2*)(canon + 24 * (k0 + site) + 2 * part) = *(const double2*)&rows[site * ROW + 2 * part];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 24; ++i) {
+                const int e = lane + 64 * i, site = e / 24, part = e - 24 * site;
+                if (k0 + site < ntotal) canon[24 * (k0 + site) + part] = rows[site * ROW + part];
+            }
         }
     } else {
         const double* c = canon + 24 * k;
@@ -145,8 +154,11 @@ static wd_status spinor_pack_t(wd_context ctx, const Geom& g, int subset, int nr
     const long long n = per * nrhs;
     const int bs = PACK_BLOCK;
     const dim3 grid((unsigned)((n + bs - 1) / bs));
-    if (unpack)
+    if (unpack && (uintptr_t)canon % sizeof(double2) == 0)
         hipLaunchKernelGGL((spinor_pack_kernel<P, true>), grid, dim3(bs), 0, ctx->stream, (double*)canon,
+                           (char*)packed, g, subset, per, n);
+    else if (unpack)
+        hipLaunchKernelGGL((spinor_pack_kernel<P, true, false>), grid, dim3(bs), 0, ctx->stream, (double*)canon,
                            (char*)packed, g, subset, per, n);
     else
         hipLaunchKernelGGL((spinor_pack_kernel<P, false>), grid, dim3(bs), 0, ctx->stream, (double*)canon,

@@ -556,3 +556,27 @@ def test_pack_and_unpack_edges(w, ctx, dims, subset, nrhs, prec):
     want = src if prec == "f64" else src.float().double()
     assert torch.equal(back[:src.numel()], want)
     assert torch.isnan(back[src.numel():]).all()
+
+
+@pytest.mark.parametrize("dims,subset,nrhs", [((2, 2, 2, 2), "even", 1), ((4, 6, 2, 10), "full", 1), ((4, 6, 2, 10), "odd", 3)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+def test_unpack_to_any_double(w, ctx, dims, subset, nrhs, prec):
+    """A canonical field that starts at an odd multiple of eight bytes takes the same values as an aligned one, and
+    nothing beside it is written."""
+    import ctypes
+    import torch
+    X, Y, Z, T = dims
+    sub, p = w.SUBSET_BY_NAME[subset], w.PREC_BY_NAME[prec]
+    n = X * Y * Z * T // (1 if subset == "full" else 2)
+    lat = w.lattice(dims, BC)
+    src = torch.from_numpy(ls.gaussian_complex((nrhs, n, 4, 3), 906, ls.STREAM_SPINOR).view(np.float64)).cuda().reshape(-1)
+    packed = w.pack(ctx, lat, sub, p, src, nrhs)
+    outs = []
+    for at in (0, 1):
+        back = torch.full((src.numel() + 65,), float("nan"), dtype=torch.float64, device="cuda")
+        assert back.data_ptr() % 16 == 0
+        w.wd_spinor_unpack(ctx.handle, ctypes.byref(lat), sub, p, nrhs, packed.data_ptr(), back.data_ptr() + 8 * at)
+        torch.cuda.synchronize()
+        outs.append(back[at:at + src.numel()])
+        assert torch.isnan(back[:at]).all() and torch.isnan(back[at + src.numel():]).all()
+    assert torch.equal(outs[0], outs[1]) and not torch.isnan(outs[0]).any()
