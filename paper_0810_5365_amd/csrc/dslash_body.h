@@ -378,23 +378,28 @@ __device__ __forceinline__ void split_hops(const DslashArgs& A, uint32_t cb, con
     HopRaw<P, R> f, b;
     hop_load<2 * MU, NT>(A, cb, c, in, gbytes, f);
     hop_load<2 * MU + 1, NT>(A, cb, c, in, gbytes, b);
-    float4 w[NV];
-    hop_half_spinor<2 * MU, DAG>(A, c, f, (T*)w);
+    T w[12];
+    float4 q[NV];
+    hop_half_spinor<2 * MU, DAG>(A, c, f, w);
+    __builtin_memcpy(q, w, sizeof(w));
 #pragma unroll
-    for (int k = 0; k < NV; ++k) lds[(2 * MU * NV + k) * 64 + lane] = w[k];
-    hop_half_spinor<2 * MU + 1, DAG>(A, c, b, (T*)w);
+    for (int k = 0; k < NV; ++k) lds[(2 * MU * NV + k) * 64 + lane] = q[k];
+    hop_half_spinor<2 * MU + 1, DAG>(A, c, b, w);
+    __builtin_memcpy(q, w, sizeof(w));
 #pragma unroll
-    for (int k = 0; k < NV; ++k) lds[((2 * MU + 1) * NV + k) * 64 + lane] = w[k];
+    for (int k = 0; k < NV; ++k) lds[((2 * MU + 1) * NV + k) * 64 + lane] = q[k];
 }
 
 template <int D, int P, bool DAG, typename T>
 __device__ __forceinline__ void split_sum(const float4* lds, int lane, T* acc)
 {
     constexpr int NV = 12 * sizeof(T) / 16;
-    float4 w[NV];
+    float4 q[NV];
 #pragma unroll
-    for (int k = 0; k < NV; ++k) w[k] = lds[(D * NV + k) * 64 + lane];
-    hop_accumulate<D, DAG>(acc, (const T*)w);
+    for (int k = 0; k < NV; ++k) q[k] = lds[(D * NV + k) * 64 + lane];
+    T w[12];
+    __builtin_memcpy(w, q, sizeof(w));
+    hop_accumulate<D, DAG>(acc, w);
     if constexpr (D + 1 < 8) split_sum<D + 1, P, DAG>(lds, lane, acc);
 }
 
