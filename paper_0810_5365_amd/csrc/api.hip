@@ -183,12 +183,13 @@ static DslashCall half_call(wd_gauge g, const void* links, int prec, int par, in
 }
 
 wd_status hop_half(wd_gauge g, int prec, int par, int dagger, int nrhs, const void* in, long long in_stride, void* out,
-                   long long out_stride, const void* x, long long x_stride, double a, double b)
+                   long long out_stride, const void* x, long long x_stride, double a, double b, int uses)
 {
     const void* links = nullptr;
     WD_TRY(gauge_links(g, prec, &links));
-    return launch_dslash(g->ctx, g->geom,
-                         half_call(g, links, prec, par, dagger, nrhs, in, in_stride, out, out_stride, x, x_stride, a, b));
+    DslashCall c = half_call(g, links, prec, par, dagger, nrhs, in, in_stride, out, out_stride, x, x_stride, a, b);
+    c.uses = uses;
+    return launch_dslash(g->ctx, g->geom, c);
 }
 
 // precision of the field a fused reduction stores
@@ -291,24 +292,24 @@ wd_status eo_finish(wd_gauge g, double kappa, const void* b, void* x, double* rr
 }
 
 wd_status op_dslash(wd_gauge g, int subset, int dagger, int prec, int nrhs, const void* in, void* out, const void* x,
-                    double a, double b)
+                    double a, double b, int uses)
 {
     const Geom& G = g->geom;
     const long long hb = (long long)half_bytes(G, prec);
     if (subset == WD_FULL) {
         for (int par = 0; par < 2; ++par) {
             WD_TRY(hop_half(g, prec, par, dagger, nrhs, (const char*)in + (1 - par) * hb, 2 * hb, (char*)out + par * hb,
-                            2 * hb, x ? (const char*)x + par * hb : nullptr, 2 * hb, a, b));
+                            2 * hb, x ? (const char*)x + par * hb : nullptr, 2 * hb, a, b, uses));
         }
         return WD_OK;
     }
     const int par = subset == WD_EVEN ? 0 : 1;
-    return hop_half(g, prec, par, dagger, nrhs, in, hb, out, hb, x, hb, a, b);
+    return hop_half(g, prec, par, dagger, nrhs, in, hb, out, hb, x, hb, a, b, uses);
 }
 
-wd_status op_M(wd_gauge g, double kappa, int subset, int dagger, int prec, int nrhs, const void* in, void* out)
+wd_status op_M(wd_gauge g, double kappa, int subset, int dagger, int prec, int nrhs, const void* in, void* out, int uses)
 {
-    if (subset == WD_FULL) return op_dslash(g, WD_FULL, dagger, prec, nrhs, in, out, in, 1.0, -kappa);
+    if (subset == WD_FULL) return op_dslash(g, WD_FULL, dagger, prec, nrhs, in, out, in, 1.0, -kappa, uses);
     const Geom& G = g->geom;
     const long long hb = (long long)half_bytes(G, prec);
     void* tmp = nullptr;
@@ -316,8 +317,8 @@ wd_status op_M(wd_gauge g, double kappa, int subset, int dagger, int prec, int n
     const int par = subset == WD_EVEN ? 0 : 1;
     // tmp (other parity) = D in ; out = in - kappa^2 D tmp.  out may be in itself: the second
     // launch reads in only as its x, at the site it writes (callers inside the library use this)
-    WD_TRY(hop_half(g, prec, 1 - par, dagger, nrhs, in, hb, tmp, hb, nullptr, 0, 0.0, 1.0));
-    return hop_half(g, prec, par, dagger, nrhs, tmp, hb, out, hb, in, hb, 1.0, -kappa * kappa);
+    WD_TRY(hop_half(g, prec, 1 - par, dagger, nrhs, in, hb, tmp, hb, nullptr, 0, 0.0, 1.0, uses));
+    return hop_half(g, prec, par, dagger, nrhs, tmp, hb, out, hb, in, hb, 1.0, -kappa * kappa, uses);
 }
 
 wd_status op_MdagM(wd_gauge g, double kappa, int subset, int prec, int nrhs, const void* in, void* out)
@@ -607,7 +608,7 @@ static wd_status op_args(wd_gauge g, int subset, int prec, int nrhs, const void*
 wd_status wd_dslash(wd_gauge g, wd_subset out_subset, int dagger, wd_prec prec, int nrhs, const void* in, void* out)
 {
     WD_TRY(op_args(g, out_subset, prec, nrhs, in, out));
-    return op_dslash(g, out_subset, dagger != 0, prec, nrhs, in, out, nullptr, 0.0, 1.0);
+    return op_dslash(g, out_subset, dagger != 0, prec, nrhs, in, out, nullptr, 0.0, 1.0, out_subset == WD_FULL ? 2 : 1);
 }
 
 wd_status wd_dslash_xpay(wd_gauge g, wd_subset out_subset, int dagger, wd_prec prec, int nrhs, const void* in,
@@ -618,7 +619,7 @@ wd_status wd_dslash_xpay(wd_gauge g, wd_subset out_subset, int dagger, wd_prec p
         set_error("wd_dslash_xpay: x is NULL");
         return WD_EINVAL;
     }
-    return op_dslash(g, out_subset, dagger != 0, prec, nrhs, in, out, x, a, b);
+    return op_dslash(g, out_subset, dagger != 0, prec, nrhs, in, out, x, a, b, out_subset == WD_FULL ? 2 : 1);
 }
 
 wd_status wd_apply_M(wd_gauge g, double kappa, wd_subset subset, int dagger, wd_prec prec, int nrhs, const void* in,
@@ -629,7 +630,7 @@ wd_status wd_apply_M(wd_gauge g, double kappa, wd_subset subset, int dagger, wd_
         set_error("wd_apply_M: in and out must not alias");
         return WD_EINVAL;
     }
-    return op_M(g, kappa, subset, dagger != 0, prec, nrhs, in, out);
+    return op_M(g, kappa, subset, dagger != 0, prec, nrhs, in, out, 2);
 }
 
 wd_status wd_apply_MdagM(wd_gauge g, double kappa, wd_subset subset, wd_prec prec, int nrhs, const void* in, void* out)

@@ -109,31 +109,18 @@ wd_status dslash_setup(const Geom& g, const DslashCall& c, const TuneParam& tp, 
     return WD_OK;
 }
 
-// What an untuned launch shape leaves open.  us per launch inside Mhat^dag Mhat, one MI355X.
-//
-// Four waves per 64 sites (split) against one: 8^3 x 16 F32 3.9 / 5.4, F64 4.9 / 5.9; 16^3 x 32 F32
-// 8.5 / 8.8, F16 6.7 / 7.3, BF16 6.2 / 7.4, F64 17.2 / 16.9; 24^3 x 48 F32 35.3 / 37.7, F16 21.3 / 22.6,
-// F64 86.8 / 82.8; 28^3 x 56 (9604 groups of 64) F32 74.0 / 75.4, F16 36.2 / 37.8; 32^3 x 64 (16 384
-// groups) F32 116.6 / 116.3, F16 67.4 / 65.2.  It hides latency, at the price of a trip through LDS
-// and, in F64, of fewer bytes in flight per register.  Several rhs: F32 gains throughout (3 on 16^3 x 32
-// 16.5 / 18.2, on 24^3 x 48 97.9 / 99.8, 16 on 16^3 x 32 89.4 / 90.2); 16-bit storage is bound by its
-// vector work once the chip is full (BF16: 3 on 16^3 x 32, 3072 groups in all, 11.7 / 12.0; 3 on
-// 24^3 x 48 47.9 / 45.0; 16 on 16^3 x 32 52.6 / 46.5).
-//
-// Non-temporal link loads leave the 256 MB last-level cache to the spinors; links that fit it beside
-// them are better kept: F32 24^3 x 48 (127 MB of links) 35.3 kept / 40.8 not, 28^3 x 56 (236 MB)
-// 81.8 / 74.0; F16 28^3 x 56 (118 MB) 36.2 / 42.0, 32^3 x 64 (201 MB) 66.8 / 65.2; F64 20^3 x 40
-// (123 MB) 36.4 / 40.7, 24^3 x 48 (255 MB) 91.2 / 82.8.  With several rhs the links are read again
-// within a launch and are kept (16 rhs on 16^3 x 32, F32 90 / 110, BF16 46 / 57).
-constexpr size_t NT_LINK_BYTES = (size_t)160 << 20;
-
 TuneParam dslash_shape(const Geom& g, const DslashCall& c, const TuneParam& tp)
 {
     TuneParam t = tp;
-    const long long groups = (long long)((g.Vh + 63) / 64) * c.nrhs;
-    const bool one = c.nrhs == 1;
-    if (t.split < 0) t.split = groups <= (c.prec == WD_F64 ? 512 : one ? 12288 : c.prec == WD_F32 ? 32768 : 4096);
-    if (t.nt < 0) t.nt = one && 8 * link_site_bytes(c.prec, c.recon) * (size_t)g.ps > NT_LINK_BYTES;
+    ShapeCall s;
+    s.prec = c.prec;
+    s.recon = c.recon;
+    s.nrhs = c.nrhs;
+    s.uses = c.uses;
+    s.groups = (long long)((g.Vh + 63) / 64) * c.nrhs;
+    s.links = 8 * link_site_bytes(c.prec, c.recon) * (size_t)g.ps;
+    s.half = half_bytes(g, c.prec) * (size_t)c.nrhs;
+    settle_shape(s, &t);
     return t;
 }
 

@@ -123,40 +123,7 @@ wd_status autotune_dslash(wd_gauge g, int prec, int nrhs, int* ntuned)
             // the one with the lowest of those wins (single short timings are noisy enough to
             // reorder candidates a few per cent apart)
             std::vector<std::pair<float, TuneParam>> cand;
-            std::vector<int> zbs{0};
-            for (int d = 2; d < G.L[2]; d *= 2)
-                if (G.L[2] % d == 0) zbs.push_back(d);
-            for (int zb : zbs)
-            for (int block = 64; block <= 256; block += 64)
-                for (int remap = 0; remap < 2; ++remap)
-                    for (int nt = 0; nt < 2; ++nt)
-                        for (int pf = 0; pf < 2; ++pf)
-                            for (int ri = (nrhs > 1 ? 0 : 1); ri < 2; ++ri) {
-                            TuneParam tp;
-                            tp.block = block;
-                            tp.remap = remap;
-                            tp.nt = nt;
-                            tp.pf = pf;
-                            tp.rhs_inner = ri;
-                            tp.zb = zb;
-                            tp.split = 0;
-                            float us;
-                            WD_TRY(time_launch(ctx, G, c, tp, reps, &us));
-                            cand.emplace_back(us, tp);
-                        }
-            {   // four waves per 64 sites: no launch-shape parameters but the remap
-                TuneParam tp;
-                tp.nt = 0;
-                tp.split = 1;
-                float us;
-                WD_TRY(time_launch(ctx, G, c, tp, reps, &us));
-                cand.emplace_back(us, tp);
-            }
-            if (mrhs_eligible(c)) {   // the matrix-core path has no launch-shape parameters
-                TuneParam tp;
-                tp.nt = 1;
-                tp.split = 0;
-                tp.mf = 1;
+            for (const TuneParam& tp : tune_candidates(nrhs, G.L[2], (long long)((G.Vh + 63) / 64) * nrhs, mrhs_eligible(c))) {
                 float us;
                 WD_TRY(time_launch(ctx, G, c, tp, reps, &us));
                 cand.emplace_back(us, tp);

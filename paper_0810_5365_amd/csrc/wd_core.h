@@ -7,6 +7,7 @@
 #include <map>
 #include <string>
 
+#include "dslash_shape.h"
 #include "wd_device.h"
 #include "wdirac.h"
 
@@ -39,20 +40,6 @@ void clear_error();
             return WD_EHIP;                                                             \
         }                                                                               \
     } while (0)
-
-// Launch shape of one kernel: workgroup size, XCD-aware block remap, and
-// non-temporal (streaming) link loads.
-struct TuneParam {
-    int block = 64;
-    int remap = 1;
-    int nt = -1;  // non-temporal link loads (-1: by the rule in dslash_shape)
-    int pf = 1;   // software-pipelined directions
-    int rhs_inner = 1;   // several rhs: interleave them with the site tiles
-    int zb = 0;          // z-blocked site traversal depth (0: natural order)
-    int mf = 0;          // 16-bit, 12-real, 16k rhs: colour multiply on the matrix cores
-    int split = -1;      // four waves per 64 sites; block, nt, pf, rhs_inner and zb then do not matter
-                         // (-1: by the rule in dslash_shape)
-};
 
 inline bool valid_prec(int p) { return p >= WD_F64 && p <= WD_BF16; }
 inline bool valid_subset(int s) { return s >= WD_FULL && s <= WD_ODD; }
@@ -122,6 +109,7 @@ struct DslashCall {
     int prec = WD_F32;
     int recon = 12;
     int gf = 0;                    // links in temporal gauge (unit t-links but the last slice)
+    int uses = 4;                  // see ShapeCall
 };
 wd_status launch_dslash(wd_context ctx, const Geom& g, const DslashCall& c);
 wd_status launch_dslash_tuned(wd_context ctx, const Geom& g, const DslashCall& c, const TuneParam& tp);

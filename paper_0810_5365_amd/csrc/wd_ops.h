@@ -5,14 +5,16 @@
 
 namespace wd {
 
-// out (parity par, nrhs half fields) = a x + b D in  (x may be null: out = b D in)
+// out (parity par, nrhs half fields) = a x + b D in  (x may be null: out = b D in).  uses, here and below: as in
+// ShapeCall, the launches of one call or solve that read the links.
 wd_status hop_half(wd_gauge g, int prec, int par, int dagger, int nrhs, const void* in, long long in_stride, void* out,
-                   long long out_stride, const void* x, long long x_stride, double a, double b);
+                   long long out_stride, const void* x, long long x_stride, double a, double b, int uses = 4);
 // D_hop on a FULL / EVEN / ODD field, optionally fused with a x + b D in
 wd_status op_dslash(wd_gauge g, int subset, int dagger, int prec, int nrhs, const void* in, void* out, const void* x,
-                    double a, double b);
+                    double a, double b, int uses = 4);
 // M (FULL) or Mhat (EVEN / ODD), or their daggers
-wd_status op_M(wd_gauge g, double kappa, int subset, int dagger, int prec, int nrhs, const void* in, void* out);
+wd_status op_M(wd_gauge g, double kappa, int subset, int dagger, int prec, int nrhs, const void* in, void* out,
+               int uses = 4);
 // out = Mhat in (EVEN / ODD) or M in (FULL), or their daggers, one rhs, with the reduction
 // `red` of the result summed by the last launch(es) into dres[slot ..] and hres[slot ..] (not
 // fetched: synchronise before reading hres): RED_NORM ||out||^2; RED_XDOT <out, in>,

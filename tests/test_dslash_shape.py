@@ -1,0 +1,162 @@
+"""CPU: the rule by which an untuned dslash launch chooses its shape, and the shapes the autotuner times."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PREC = {"f64": 0, "f32": 1, "f16": 2, "bf16": 3}
+REAL = {"f64": 8, "f32": 4, "f16": 2, "bf16": 2}
+SITE = {"f64": 192, "f32": 96, "f16": 52, "bf16": 52}
+USES = {"hop_even": 1, "hop_full": 2, "m_full": 2, "mdagm_even": 4}
+FIELDS = ("block", "remap", "nt", "pf", "rhs_inner", "zb", "mf", "split")
+
+SHIM = """
+#include "dslash_shape.h"
+static void put(const wd::TuneParam& t, int* o)
+{
+    const int v[8] = {t.block, t.remap, t.nt, t.pf, t.rhs_inner, t.zb, t.mf, t.split};
+    for (int i = 0; i < 8; ++i) o[i] = v[i];
+}
+extern "C" void choose(int prec, int recon, int nrhs, int uses, long long groups, size_t links, size_t half, int* o)
+{
+    wd::ShapeCall c;
+    c.prec = prec; c.recon = recon; c.nrhs = nrhs; c.uses = uses; c.groups = groups; c.links = links; c.half = half;
+    wd::TuneParam t;
+    wd::settle_shape(c, &t);
+    put(t, o);
+}
+extern "C" int candidates(int nrhs, int z, long long groups, int matrix, int* o, int most)
+{
+    const std::vector<wd::TuneParam> v = wd::tune_candidates(nrhs, z, groups, matrix != 0);
+    for (size_t i = 0; i < v.size() && (int)i < most; ++i) put(v[i], o + 8 * i);
+    return (int)v.size();
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shapes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shape")
+    src, lib = str(d / "shim.cpp"), str(d / "shim.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                           "-I" + os.path.join(ROOT, "paper_0810_5365_amd", "csrc"), "-I" + os.path.join(ROOT, "include"),
+                           src, "-o", lib])
+    L = ctypes.CDLL(lib)
+    LL, Z, P = ctypes.c_longlong, ctypes.c_size_t, ctypes.POINTER(ctypes.c_int)
+    L.choose.argtypes = [ctypes.c_int] * 4 + [LL, Z, Z, P]
+    L.candidates.argtypes = [ctypes.c_int, ctypes.c_int, LL, ctypes.c_int, P, ctypes.c_int]
+    return L
+
+
+def sizes(dims, prec, recon, nrhs):
+    """64-site groups, bytes of the links and of a half field (the planes' padding left out)."""
+    Vh = dims[0] * dims[1] * dims[2] * dims[3] // 2
+    return (Vh + 63) // 64 * nrhs, 8 * Vh * recon * REAL[prec], Vh * SITE[prec] * nrhs
+
+
+def choose(L, dims, prec, recon, nrhs, uses):
+    o = (ctypes.c_int * 8)()
+    L.choose(PREC[prec], recon, nrhs, uses, *sizes(dims, prec, recon, nrhs), o)
+    return dict(zip(FIELDS, o))
+
+
+def candidates(L, dims, nrhs, matrix=False):
+    o = (ctypes.c_int * (8 * 4096))()
+    n = L.candidates(nrhs, dims[2], (dims[0] * dims[1] * dims[2] * dims[3] // 2 + 63) // 64 * nrhs, matrix, o, 4096)
+    assert 0 < n <= 4096
+    return [dict(zip(FIELDS, o[8 * i:8 * i + 8])) for i in range(n)]
+
+
+# us per call on one MI355X, three sets of links and fields in turn: one wave per 64 sites with streamed links as
+# it was before the four-wave kernel, then one wave with kept and with streamed links, four waves with either
+MEASURED = [
+    ("hop_even", "14x16x18x34", "f64", 18, 1, 23.3, 24.5, 23.4, 23.4, 23.1),
+    ("hop_full", "14x16x18x34", "f64", 18, 1, 46.7, 47.3, 46.8, 44.9, 46.2),
+    ("m_full", "14x16x18x34", "f64", 18, 1, 49.1, 51.1, 49.1, 48.9, 48.0),
+    ("mdagm_even", "14x16x18x34", "f64", 18, 1, 98.7, 88.6, 99.0, 85.8, 96.0),
+    ("hop_even", "16x16x16x32", "f64", 18, 1, 20.5, 23.0, 20.6, 21.1, 20.7),
+    ("hop_full", "16x16x16x32", "f64", 18, 1, 40.1, 44.2, 41.0, 40.7, 41.1),
+    ("m_full", "16x16x16x32", "f64", 18, 1, 43.0, 47.9, 43.4, 44.6, 43.1),
+    ("mdagm_even", "16x16x16x32", "f64", 18, 1, 85.3, 89.4, 84.5, 80.3, 86.0),
+    ("hop_even", "18x22x12x36", "f64", 12, 1, 23.6, 24.4, 23.6, 25.3, 25.4),
+    ("hop_full", "18x22x12x36", "f64", 12, 1, 47.2, 46.6, 47.3, 49.6, 50.9),
+    ("m_full", "18x22x12x36", "f64", 12, 1, 50.2, 50.0, 50.3, 54.1, 54.3),
+    ("hop_even", "18x22x12x36", "f64", 18, 1, 27.3, 30.0, 27.4, 30.2, 28.2),
+    ("hop_full", "18x22x12x36", "f64", 18, 1, 54.6, 58.1, 54.8, 56.5, 56.1),
+    ("m_full", "18x22x12x36", "f64", 18, 1, 58.2, 63.2, 58.1, 62.2, 58.3),
+    ("hop_even", "20x20x20x40", "f32", 12, 2, 34.7, 34.0, 34.6, 32.9, 31.8),
+    ("hop_even", "20x20x20x40", "f64", 12, 1, 41.1, 46.8, 41.0, 47.0, 41.7),
+    ("hop_even", "20x20x20x40", "bf16", 18, 3, 32.7, 28.2, 33.1, 27.9, 29.5),
+    ("hop_even", "20x20x20x40", "f16", 18, 3, 33.2, 29.2, 33.3, 28.7, 30.0),
+    ("hop_even", "20x20x20x40", "f32", 18, 1, 26.0, 27.3, 25.1, 26.7, 24.6),
+    ("hop_full", "20x20x20x40", "f32", 18, 1, 52.1, 52.2, 52.2, 48.7, 49.0),
+    ("m_full", "20x20x20x40", "f32", 18, 1, 54.4, 56.4, 52.9, 54.1, 51.0),
+    ("hop_even", "20x20x20x40", "f32", 18, 2, 41.5, 40.0, 41.5, 40.3, 38.1),
+    ("hop_even", "22x22x22x22", "f64", 12, 1, 29.5, 31.7, 29.4, 35.5, 33.7),
+    ("hop_full", "22x22x22x22", "f64", 12, 1, 59.7, 63.7, 59.8, 69.6, 67.7),
+    ("m_full", "22x22x22x22", "f64", 12, 1, 64.6, 70.8, 64.1, 75.5, 73.0),
+    ("hop_even", "22x22x22x22", "f64", 18, 1, 36.1, 42.0, 36.4, 42.4, 38.4),
+    ("hop_full", "22x22x22x22", "f64", 18, 1, 72.6, 79.0, 72.9, 77.1, 77.0),
+    ("m_full", "22x22x22x22", "f64", 18, 1, 77.1, 85.6, 77.1, 84.6, 80.2),
+    ("hop_even", "24x24x24x32", "bf16", 12, 3, 38.4, 38.2, 38.7, 38.6, 38.4),
+    ("hop_even", "24x24x24x32", "f16", 12, 3, 39.5, 39.4, 40.1, 41.0, 40.6),
+    ("hop_even", "24x24x24x32", "f32", 12, 1, 27.9, 29.1, 27.0, 27.4, 25.6),
+    ("hop_full", "24x24x24x32", "f32", 12, 1, 56.0, 57.1, 56.1, 54.4, 51.3),
+    ("m_full", "24x24x24x32", "f32", 12, 1, 60.4, 63.1, 58.9, 61.2, 55.0),
+    ("hop_even", "24x24x24x32", "bf16", 18, 2, 30.3, 29.6, 30.9, 28.5, 28.4),
+    ("hop_even", "24x24x24x32", "f16", 18, 2, 31.1, 29.6, 31.2, 29.0, 29.1),
+    ("hop_even", "24x24x24x32", "f32", 18, 1, 33.6, 37.7, 33.6, 37.1, 32.7),
+    ("m_full", "24x24x24x32", "f32", 18, 1, 72.3, 77.3, 70.9, 75.3, 68.7),
+    ("hop_even", "24x24x24x48", "bf16", 12, 1, 24.7, 23.4, 23.4, 22.7, 22.8),
+    ("hop_full", "24x24x24x48", "bf16", 12, 1, 49.2, 46.5, 47.0, 44.6, 46.0),
+    ("m_full", "24x24x24x48", "bf16", 12, 1, 53.0, 50.4, 51.2, 48.4, 48.7),
+    ("hop_even", "24x24x24x48", "bf16", 12, 2, 39.2, 40.0, 39.6, 39.9, 38.8),
+    ("hop_even", "24x24x24x48", "f16", 12, 1, 25.0, 24.2, 24.3, 24.1, 24.2),
+    ("hop_full", "24x24x24x48", "f16", 12, 1, 50.0, 49.4, 48.5, 47.3, 48.1),
+    ("m_full", "24x24x24x48", "f16", 12, 1, 53.1, 52.1, 51.9, 51.0, 51.0),
+    ("hop_even", "24x24x24x48", "f16", 12, 2, 40.6, 41.4, 41.0, 42.0, 41.5),
+    ("hop_even", "24x24x24x48", "f32", 12, 1, 39.3, 45.1, 39.2, 44.7, 38.2),
+    ("hop_even", "24x24x24x48", "bf16", 18, 1, 27.9, 29.1, 27.2, 29.3, 26.9),
+    ("hop_full", "24x24x24x48", "bf16", 18, 1, 55.7, 56.3, 54.3, 53.8, 53.6),
+    ("m_full", "24x24x24x48", "bf16", 18, 1, 59.5, 62.2, 58.3, 58.6, 56.0),
+    ("hop_even", "24x24x24x48", "f16", 18, 1, 28.5, 29.2, 27.2, 29.5, 27.1),
+    ("hop_full", "24x24x24x48", "f16", 18, 1, 57.1, 57.0, 54.5, 53.8, 54.1),
+    ("m_full", "24x24x24x48", "f16", 18, 1, 60.8, 62.5, 58.0, 59.6, 56.8),
+    ("mdagm_even", "24x24x24x48", "f32", 18, 1, 209.4, 201.2, 208.4, 198.1, 209.3),
+    ("hop_even", "26x30x22x44", "f32", 12, 1, 45.1, 50.7, 44.6, 50.2, 43.5),
+    ("hop_even", "26x30x22x44", "bf16", 18, 1, 30.6, 34.6, 31.5, 32.9, 30.4),
+    ("hop_even", "26x30x22x44", "f16", 18, 1, 31.0, 34.9, 32.0, 32.9, 30.4),
+    ("hop_even", "28x28x28x40", "bf16", 12, 1, 29.3, 31.2, 29.2, 30.1, 28.5),
+    ("hop_even", "28x28x28x40", "bf16", 12, 2, 51.1, 53.2, 52.1, 52.2, 50.8),
+    ("hop_even", "28x28x28x40", "f16", 12, 1, 30.0, 33.2, 31.0, 32.0, 30.4),
+    ("m_full", "28x28x28x40", "f16", 12, 1, 64.4, 70.7, 67.4, 67.7, 65.5),
+    ("hop_even", "28x28x28x40", "f16", 12, 2, 52.7, 54.7, 53.3, 56.6, 54.0),
+    ("hop_even", "28x28x28x40", "bf16", 18, 1, 34.6, 39.0, 34.7, 38.3, 33.8),
+    ("m_full", "28x28x28x40", "bf16", 18, 1, 74.4, 79.9, 74.8, 77.5, 71.8),
+    ("hop_even", "28x28x28x40", "bf16", 18, 2, 58.6, 60.4, 60.4, 58.2, 55.0),
+    ("hop_even", "28x28x28x40", "f16", 18, 1, 35.0, 39.5, 35.0, 38.7, 34.2),
+    ("m_full", "28x28x28x40", "f16", 18, 1, 75.3, 80.1, 74.9, 78.6, 72.6),
+    ("hop_even", "28x28x28x40", "f16", 18, 2, 58.9, 60.6, 61.1, 59.1, 56.1),
+    ("hop_even", "28x28x28x56", "bf16", 12, 1, 40.2, 44.8, 40.1, 43.4, 39.6),
+    ("hop_even", "28x28x28x56", "f16", 12, 1, 41.1, 45.5, 40.9, 45.8, 41.1),
+    ("hop_even", "28x28x28x56", "f32", 18, 1, 98.0, 105.1, 97.5, 108.8, 100.9),
+    ("hop_even", "30x32x34x40", "bf16", 12, 1, 41.8, 46.4, 41.4, 45.6, 40.4),
+    ("mdagm_even", "30x32x34x40", "bf16", 12, 1, 175.1, 163.0, 175.1, 167.2, 169.6),
+    ("hop_even", "30x32x34x40", "f16", 12, 1, 42.4, 47.2, 42.2, 47.5, 43.2),
+    ("mdagm_even", "30x32x34x40", "f16", 12, 1, 177.9, 168.8, 178.0, 173.2, 181.9),
+]
+
+
+@pytest.mark.parametrize("row", MEASURED, ids=lambda r: "-".join(map(str, r[:5])))
+def test_untuned_choice_is_not_slower_than_before(shapes, row):
+    """Runs of one kernel differ by up to 1% at one size in twenty; the 16-bit and F64 one-wave kernels by 2.3%
+    from what they were on single lattices."""
+    op, dims, prec, recon, nrhs, before = row[:6]
+    c = choose(shapes, [int(x) for x in dims.split("x")], prec, recon, nrhs, USES[op])
+    t = dict(zip(((0, 0), (0, 1), (1, 0), (1, 1)), row[6:]))[(c["split"], c["nt"])]
+    assert t <= 1.025 * before, c
