@@ -116,9 +116,16 @@ inline std::vector<TuneParam> tune_candidates(int nrhs, int z, long long groups,
                             all.push_back(tp);
                         }
     tp = TuneParam();
-    tp.nt = 0;
     tp.split = 1;
-    all.push_back(tp);
+    if (groups < 1ll << 24)   // 256 work-items a group, 2^32 a launch
+        for (int remap = 0; remap < 2; ++remap)
+            for (int nt = 0; nt < 2; ++nt)
+                for (int ri = (nrhs > 1 ? 0 : 1); ri < 2; ++ri) {
+                    tp.remap = remap;
+                    tp.nt = nt;
+                    tp.rhs_inner = ri;
+                    all.push_back(tp);
+                }
     if (matrix) {   // no launch-shape parameters
         tp = TuneParam();
         tp.nt = 1;

@@ -160,3 +160,34 @@ def test_untuned_choice_is_not_slower_than_before(shapes, row):
     c = choose(shapes, [int(x) for x in dims.split("x")], prec, recon, nrhs, USES[op])
     t = dict(zip(((0, 0), (0, 1), (1, 0), (1, 1)), row[6:]))[(c["split"], c["nt"])]
     assert t <= 1.025 * before, c
+
+
+def test_tuner_times_the_untuned_choice(shapes):
+    """Whatever shape the rule gives a launch is among those the autotuner times for it: tuning cannot make a
+    launch slower than the rule's.  (The rule leaves a four-wave launch's block, pf and zb at their defaults.)"""
+    rng = random.Random(5)
+    dims = [(8, 8, 8, 16), (28, 28, 28, 40), (28, 28, 28, 56), (32, 32, 32, 64)]
+    dims += [tuple(2 * rng.randint(1, 24) for _ in range(4)) for _ in range(40)]
+    seen = set()
+    for d in dims:
+        for nrhs in (1, 2, 3, 6, 16):
+            timed = candidates(shapes, d, nrhs)
+            for prec in PREC:
+                for recon in (12, 18):
+                    for uses in (1, 2, 4):
+                        c = choose(shapes, d, prec, recon, nrhs, uses)
+                        assert c in timed, (d, nrhs, prec, recon, uses, c)
+                        seen.add((c["split"], c["nt"], nrhs > 1))
+    assert len(seen) == 8   # each of the four shapes, with one and with several rhs
+
+
+def test_tuner_times_every_form_of_the_four_wave_kernel(shapes):
+    """It has a link load, a block order and, with several rhs, an interleaving of its own; its four times as many
+    work-items stay below the 2^32 that a launch can have; one matrix-core entry where that kernel can run."""
+    for nrhs in (1, 3):
+        forms = [(c["nt"], c["remap"], c["rhs_inner"]) for c in candidates(shapes, (8, 8, 8, 16), nrhs) if c["split"]]
+        assert sorted(forms) == sorted((nt, remap, ri) for nt in (0, 1) for remap in (0, 1)
+                                       for ri in ((1,) if nrhs == 1 else (0, 1)))
+    assert not any(c["split"] for c in candidates(shapes, (32, 32, 32, 64), 1024))   # 2^24 groups of four waves
+    assert any(c["split"] for c in candidates(shapes, (32, 32, 32, 64), 1023))
+    assert [c["mf"] for c in candidates(shapes, (8, 8, 8, 16), 16, True)].count(1) == 1
