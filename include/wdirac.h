@@ -415,9 +415,11 @@ wd_status wd_tune_load(wd_context ctx, const char* path);
 /* Look up one tuning entry by key; fills out6 = {block, remap, nt, pf,
  * rhs_inner, zb} and returns 1, or returns 0 if the key is absent. */
 int wd_tune_get(wd_context ctx, const char* key, int* out6);
-/* The same with up to n values {block, remap, nt, pf, rhs_inner, zb, mf}, mf = 1
+/* The same with up to n values {block, remap, nt, pf, rhs_inner, zb, mf, split}, mf = 1
  * when the dslash runs its colour multiply on the matrix cores (16-bit storage,
- * 12-real links, a multiple of 16 rhs); returns 1, or 0 if the key is absent. */
+ * 12-real links, a multiple of 16 rhs), and an eighth, split = 1 when it runs four
+ * waves per 64 sites (block, pf and zb are then those of the plain kernel's fastest
+ * shape, for the launches that have only that one); returns 1, or 0 if the key is absent. */
 int wd_tune_get_n(wd_context ctx, const char* key, int* out, int n);
 
 /* ---- environment overrides (measurement and testing; results do not change, except as noted) ----

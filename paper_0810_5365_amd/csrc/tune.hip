@@ -146,6 +146,14 @@ wd_status autotune_dslash(wd_gauge g, int prec, int nrhs, int* ntuned)
                     best = cand[k].second;
                 }
             }
+            if (best.split)   // launches that have only the plain kernel (slabs) take its fastest shape from here
+                for (const auto& t : cand)
+                    if (!t.second.split && !t.second.mf) {
+                        best.block = t.second.block;
+                        best.pf = t.second.pf;
+                        best.zb = t.second.zb;
+                        break;
+                    }
             ctx->tune[dslash_key(G, prec, g->recon, nrhs, dagger, xpay)] = best;
             ++*ntuned;
         }
@@ -199,8 +207,8 @@ int wd_tune_get_n(wd_context ctx, const char* key, int* out, int n)
     auto it = ctx->tune.find(key);
     if (it == ctx->tune.end()) return 0;
     const TuneParam& tp = it->second;
-    const int v[7] = {tp.block, tp.remap, tp.nt, tp.pf, tp.rhs_inner, tp.zb, tp.mf};
-    for (int i = 0; i < n && i < 7; ++i) out[i] = v[i];
+    const int v[8] = {tp.block, tp.remap, tp.nt, tp.pf, tp.rhs_inner, tp.zb, tp.mf, tp.split};
+    for (int i = 0; i < n && i < 8; ++i) out[i] = v[i];
     return 1;
 }
 

@@ -357,10 +357,10 @@ def dslash_key(dims, prec, recon, nrhs, dagger, xpay):
 
 
 def tune_get(ctx, key):
-    out = (ctypes.c_int * 7)()
-    if wd_tune_get_n(ctx.handle, key.encode(), out, 7):
+    out = (ctypes.c_int * 8)()
+    if wd_tune_get_n(ctx.handle, key.encode(), out, 8):
         return {"block": out[0], "remap": out[1], "nt": out[2], "pf": out[3], "rhs_inner": out[4], "zb": out[5],
-                "mfma": out[6]}
+                "mfma": out[6], "split": out[7]}
     return None
 
 

@@ -76,3 +76,25 @@ def test_every_launch_shape_is_correct(block, remap, nt, pf, zb, monkeypatch):
             assert orc.rel_l2(got[r], ref[r]) < tol
         g.close()
     ctx.close()
+
+
+def test_four_wave_entries_survive_the_table(tmp_path):
+    """Which kernel an entry runs is read, reported and written; a file from before there were two means the one
+    there was."""
+    from paper_0810_5365_amd import wdirac as w
+    rows = [("a", 64, 1, 0, 1, 1, 0, 0, 1), ("b", 256, 0, 1, 0, 0, 4, 0, 0), ("c", 128, 1, 1, 1, 1, 2, 0, None)]
+    names = ("block", "remap", "nt", "pf", "ri", "zb", "mf", "sp")
+    first, second = str(tmp_path / "1.json"), str(tmp_path / "2.json")
+    with open(first, "w") as f:
+        for r in rows:
+            f.write('  {"key": "%s", %s},\n' % (r[0], ", ".join('"%s": %d' % kv for kv in zip(names, r[1:]) if kv[1] is not None)))
+    for load, save in ((first, second), (second, None)):
+        ctx = w.Context(0)
+        w.wd_tune_load(ctx.handle, load.encode())
+        for r in rows:
+            e = w.tune_get(ctx, r[0])
+            want = [v or 0 for v in r[1:]]
+            assert [e[k] for k in ("block", "remap", "nt", "pf", "rhs_inner", "zb", "mfma", "split")] == want
+        if save:
+            w.wd_tune_save(ctx.handle, save.encode())
+        ctx.close()
