@@ -327,7 +327,7 @@ __device__ __forceinline__ void wave_lds_sync()
 // 8 -> 8 channels, 8 samples on 16^3 x 32: 427 us, against 1930 us for a vector kernel that walked
 // the sites once per path and input channel; 4 -> 8: 255 us against 1590 us.  At 512 sites (one
 // workgroup's work) the launch and its sum take 14 us whatever the channels, against 46 us for
-// 8 -> 8 and 7 us for 1 -> 2 before.
+// 8 -> 8 before; 1 -> 2 takes 8 us on the vector units (below).
 struct WgArgs {
     const char* gauge;      // packed float32 links
     const float2* raw;      // the field that is not transported, craw channels
@@ -649,6 +649,105 @@ __global__ void __launch_bounds__(1024) wgrad_finish_kernel(const double* __rest
     const int a = raw_gout ? rc : cc, b = raw_gout ? cc : rc;
     const int pw = raw_gout || path == 0 ? path : (path <= 4 ? path + 4 : path - 4);
     gW[(pw * cout + a) * cin + b] = make_float2((float)re, (float)im);
+}
+
+// ---- weight gradients of few channels on few sites, on the vector units ------------------
+// Grid (workgroups, 9 paths), a site a work-item, one input channel after another: 2 COUT sums a
+// work-item, then the workgroup's.  Factors as above, float32 with exact float64 products and sums.
+// The 14 us of the matrix-core launches are their staging and 48-product chain whatever the size; here
+// nothing is staged (wgrad_vector has the sizes).
+template <int R, int COUT>
+__global__ void __launch_bounds__(256) wgrad_vector_kernel(PTArgs A, const float2* __restrict__ gout, int nsamples,
+                                                           double* __restrict__ partials)
+{
+    const int path = blockIdx.y;
+    const uint32_t Vh = (uint32_t)A.g.Vh;
+    const long long nsites = 2ll * Vh * nsamples;
+    __shared__ double lds[2 * COUT][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int b = 0; b < A.cin; ++b) {
+        double acc[2 * COUT];
+#pragma unroll
+        for (int i = 0; i < 2 * COUT; ++i) acc[i] = 0.0;
+        for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < nsites; k += (long long)gridDim.x * 256) {
+            const int n = (int)(k / (2 * Vh));
+            const uint32_t idx = (uint32_t)(k - (long long)n * 2 * Vh);
+            const int par = idx >= Vh ? 1 : 0;
+            const uint32_t cb = idx - (uint32_t)par * Vh;
+            const float2* in = A.in + (size_t)n * A.in_sample;
+            const float2* go = gout + (size_t)n * A.out_sample;
+            float t[6];
+            if (path == 0) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float2 q = in[fidx(b, par, c, Vh, cb)];
+                    t[2 * c] = q.x;
+                    t[2 * c + 1] = q.y;
+                }
+            } else {
+                int c[4];
+                cb_coords(A.g, cb, par, c);
+                const int mu = (path - 1) & 3;
+                const bool fwd = path <= 4;
+                bool edge;
+                const uint32_t nb = path_neighbour(A.g, cb, c, path, &edge);
+                float u[18], v[6];
+                LinkIO<P_F32, R, false>::load(A.gauge + (size_t)(2 * mu + (fwd ? par : 1 - par)) * link_site_bytes(P_F32, R) * A.g.ps,
+                                              A.g.ps, fwd ? cb : nb, u);
+#pragma unroll
+                for (int k3 = 0; k3 < 3; ++k3) {
+                    const float2 q = in[fidx(b, 1 - par, k3, Vh, nb)];
+                    v[2 * k3] = q.x;
+                    v[2 * k3 + 1] = q.y;
+                }
+                mat_vec(u, v, t, !fwd);
+                const float s = edge ? A.g.bcf[mu] : 1.0f;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) t[i] *= s;
+            }
+#pragma unroll
+            for (int a = 0; a < COUT; ++a) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {   // gout conj(t)
+                    const float2 q = go[fidx(a, par, c, Vh, cb)];
+                    const double gr = q.x, gi = q.y, tr = t[2 * c], ti = t[2 * c + 1];
+                    acc[2 * a] += gr * tr;
+                    acc[2 * a] += gi * ti;
+                    acc[2 * a + 1] += gi * tr;
+                    acc[2 * a + 1] -= gr * ti;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * COUT; ++i) {
+            double s = acc[i];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (lane == 0) lds[i][wave] = s;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2 * COUT)
+            partials[((size_t)(path * A.cin + b) * 2 * COUT + threadIdx.x) * gridDim.x + blockIdx.x] =
+                ((lds[threadIdx.x][0] + lds[threadIdx.x][1]) + lds[threadIdx.x][2]) + lds[threadIdx.x][3];
+        __syncthreads();
+    }
+}
+
+// gW[p][a][b] from the partials [p][b][a][re/im][workgroup], in a fixed order.
+__global__ void wgrad_vector_finish_kernel(const double* __restrict__ partials, int nblk, int cin, int cout,
+                                           float2* __restrict__ gW)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;   // over (p, b, a)
+    if (i >= 9 * cin * cout) return;
+    const int p = i / (cin * cout), r = i - p * cin * cout, b = r / cout, a = r - b * cout;
+    const double* pr = partials + (size_t)2 * i * nblk;
+    const double* pi = pr + nblk;
+    double re = 0.0, im = 0.0;
+    for (int k = 0; k < nblk; ++k) {
+        re += pr[k];
+        im += pi[k];
+    }
+    gW[(p * cout + a) * cin + b] = make_float2((float)re, (float)im);
 }
 
 // One path in two halves so that the loads of path p + 1 are in flight while path p is
@@ -1139,6 +1238,37 @@ static bool wgrad_split(long long ngroups, int tc)
     return 0.28 * (double)units < (double)whole;
 }
 
+// Few channels on few sites go to the vector kernel, and 1 -> 1 on many where only the reads count.  us, vector /
+// matrix cores, 12-real links: 1 -> 1 512 sites 8 / 14, 8192 9 / 14, 41 472 36 / 15, 524 288 89 / 105 (18-real 107 / 105),
+// 589 824 106 / 124; 2 -> 3 8192 13 / 14, 13 440 25 / 15; 1 -> 8 8192 14 / 14, 13 440 26 / 15.
+static bool wgrad_vector(int recon, int cin, int cout, long long nsites)
+{
+    if (cin * cout == 1 && recon == 12 && nsites >= 400000) return true;
+    return cin <= 2 && cin * cout <= 8 && nsites <= 8192;
+}
+
+template <int R>
+static wd_status wgrad_vector_r(wd_context ctx, const PTArgs& A, int cout, const float2* gout, int nsamples, float2* gW)
+{
+    long long nblk = (2ll * A.g.Vh * nsamples + 255) / 256;
+    if (nblk > 512) nblk = 512;
+    void* part;
+    WD_TRY(ws_get(ctx, "ptconv.partials", (size_t)9 * A.cin * 2 * cout * nblk * sizeof(double), &part));
+    const dim3 grid((unsigned)nblk, 9), block(256);
+    switch (cout) {
+#define WD_PT(C) case C: hipLaunchKernelGGL((wgrad_vector_kernel<R, C>), grid, block, 0, ctx->stream, A, gout, nsamples, (double*)part); break;
+        WD_PT(1) WD_PT(2) WD_PT(3) WD_PT(4) WD_PT(8)
+#undef WD_PT
+    default: set_error("ptconv: C_out = %d not supported", cout); return WD_EUNSUPPORTED;
+    }
+    WD_LAUNCHED();
+    const int n = 9 * A.cin * cout;
+    hipLaunchKernelGGL(wgrad_vector_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, ctx->stream, (const double*)part,
+                       (int)nblk, A.cin, cout, gW);
+    WD_LAUNCHED();
+    return WD_OK;
+}
+
 template <int R>
 static wd_status wgrad_r(wd_context ctx, WgArgs& A, int tc, int* nblk, double** part)
 {
@@ -1271,6 +1401,17 @@ wd_status wd_ptconv_backward(wd_gauge g, int cin, int cout, wd_prec wprec, int n
     if (gW) {
         const void* links;
         WD_TRY(gauge_links(g, WD_F32, &links));
+        if (wgrad_vector(g->recon, cin, cout, 2ll * g->geom.Vh * nsamples)) {
+            PTArgs A{};
+            A.gauge = (const char*)links;
+            A.in = (const float2*)in;
+            A.g = g->geom;
+            A.cin = cin;
+            A.in_sample = (long long)cin * 6 * g->geom.Vh;
+            A.out_sample = (long long)cout * 6 * g->geom.Vh;
+            return g->recon == 12 ? wgrad_vector_r<12>(ctx, A, cout, (const float2*)gout, nsamples, (float2*)gW)
+                                  : wgrad_vector_r<18>(ctx, A, cout, (const float2*)gout, nsamples, (float2*)gW);
+        }
         // the side with fewer channels is transported
         const bool raw_gout = cin <= cout;
         WgArgs A{};

@@ -266,3 +266,20 @@ def test_weight_gradient_launch_shapes(dims, cin, cout, n, recon):
     assert orc.rel_l2(got[..., 0] + 1j * got[..., 1], ref) < 1e-5
     g.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("dims,cin,cout,n,recon", [
+    # the vector kernel: every output width, both link forms, a remainder of its workgroups, its largest launch
+    ((2, 2, 2, 2), 1, 1, 1, 12),
+    ((4, 6, 2, 10), 1, 2, 3, 18),
+    ((4, 6, 2, 10), 2, 3, 1, 12),
+    ((4, 4, 4, 8), 2, 4, 2, 18),
+    ((8, 8, 8, 8), 1, 8, 2, 12),        # 8192 sites
+    ((4, 4, 4, 10), 2, 1, 12, 12),      # 7680 sites in twelve samples
+    ((10, 4, 6, 6), 1, 8, 6, 12),       # 8640 sites: on the matrix cores
+    ((16, 16, 16, 16), 1, 1, 7, 12),    # 458 752 sites, 1 -> 1: the vector kernel again, up to four sites a work-item
+])
+def test_weight_gradient_kernel_choice(dims, cin, cout, n, recon):
+    """Each kernel of the weight gradient on both sides of where another takes over, against the oracle; the same
+    tolerance as above, for the same sums."""
+    test_weight_gradient_launch_shapes(dims, cin, cout, n, recon)
