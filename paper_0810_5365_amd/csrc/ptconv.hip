@@ -1225,22 +1225,19 @@ wd_status launch_spinor_features(wd_context ctx, const Geom& g, int nsamples, vo
 static bool ok_channels(int c) { return c == 1 || c == 2 || c == 3 || c == 4 || c == 8; }
 
 // A 256-CU chip holds 2048 of the kernel's waves at once (two per SIMD, 120 KB of LDS per
-// workgroup), so a launch takes as many rounds as its waves go over 2048.  A wave with all units takes
-// 50-60 us per group (8 -> 8), one with a single unit about 14 us, as it stages the untransported
-// field and waits for its first loads each time: the split pays with few groups.  Measured, 8 -> 8:
-// 420 groups 30 us split and 65 us whole, 1368 groups 80 and 68; 4 -> 8: 24 and 37, 41 and 41.
+// workgroup).  A wave with all units takes 50-60 us per group (8 -> 8), one with a single unit about
+// 14 us, as it stages the untransported field and waits for its first loads each time: the split pays
+// with few groups, and with its three units of two channels always.  us, split / whole: 8 -> 8 420
+// groups 29 / 56, 1024 53 / 57, 1176 70 / 58, 2352 135 / 92; 4 -> 8 420 24 / 37, 1024 33 / 37, 1176
+// 41 / 38, 2352 80 / 59; 2 -> 8 420 16 / 31, 1024 23 / 34, 1716 40 / 39, 2352 54 / 59, 9216 141 / 153.
 constexpr int WG_SLOTS = 2048;
 
-static bool wgrad_split(long long ngroups, int tc)
-{
-    const long long whole = (ngroups + WG_SLOTS - 1) / WG_SLOTS;
-    const long long units = (ngroups * wg_units(tc) + WG_SLOTS - 1) / WG_SLOTS;
-    return 0.28 * (double)units < (double)whole;
-}
+static bool wgrad_split(long long ngroups, int tc) { return tc == 2 || ngroups <= 1100; }
 
-// Few channels on few sites go to the vector kernel, and 1 -> 1 on many where only the reads count.  us, vector /
-// matrix cores, 12-real links: 1 -> 1 512 sites 8 / 14, 8192 9 / 14, 41 472 36 / 15, 524 288 89 / 105 (18-real 107 / 105),
-// 589 824 106 / 124; 2 -> 3 8192 13 / 14, 13 440 25 / 15; 1 -> 8 8192 14 / 14, 13 440 26 / 15.
+// Few channels on few sites go to the vector kernel, and 1 -> 1 on many, where only the reads count.
+// us, vector / matrix cores, 12-real links: 1 -> 1 512 sites 8 / 14, 8192 9 / 14, 41 472 36 / 15, 524 288
+// 89 / 105 (18-real 107 / 105), 589 824 106 / 124; 2 -> 3 8192 13 / 14, 13 440 25 / 15; 1 -> 8 8192
+// 14 / 14, 13 440 26 / 15.
 static bool wgrad_vector(int recon, int cin, int cout, long long nsites)
 {
     if (cin * cout == 1 && recon == 12 && nsites >= 400000) return true;
@@ -1278,7 +1275,6 @@ static wd_status wgrad_r(wd_context ctx, WgArgs& A, int tc, int* nblk, double** 
     A.partials = *part;
     const dim3 grid(*nblk, split ? wg_units(tc) : 1), block(64 * WG_WAVES);
     switch (tc + (split ? 1 : 0)) {
-    case 2: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 2, false>), grid, block, 0, ctx->stream, A); break;
     case 3: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 2, true>), grid, block, 0, ctx->stream, A); break;
     case 4: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 4, false>), grid, block, 0, ctx->stream, A); break;
     case 5: hipLaunchKernelGGL((ptconv_wgrad_kernel<R, 4, true>), grid, block, 0, ctx->stream, A); break;

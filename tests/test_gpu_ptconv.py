@@ -278,6 +278,15 @@ def test_weight_gradient_launch_shapes(dims, cin, cout, n, recon):
     ((4, 4, 4, 10), 2, 1, 12, 12),      # 7680 sites in twelve samples
     ((10, 4, 6, 6), 1, 8, 6, 12),       # 8640 sites: on the matrix cores
     ((16, 16, 16, 16), 1, 1, 7, 12),    # 458 752 sites, 1 -> 1: the vector kernel again, up to four sites a work-item
+    # the matrix-core kernel: split up to 1100 groups, whole from there, every width of either, both link forms
+    ((10, 8, 6, 6), 8, 8, 23, 18),      # 1058 groups, split
+    ((10, 8, 6, 6), 8, 8, 24, 18),      # 1104 groups, whole
+    ((10, 8, 6, 6), 4, 8, 23, 12),
+    ((10, 8, 6, 6), 8, 3, 24, 18),
+    ((10, 8, 6, 6), 8, 2, 24, 18),      # two channels: split at any size
+    ((10, 8, 6, 6), 8, 8, 45, 12),      # 2070 groups: 22 waves past one round of the chip have a second group
+    ((10, 8, 6, 6), 4, 4, 45, 18),
+    ((10, 8, 6, 6), 2, 8, 45, 12),
 ])
 def test_weight_gradient_kernel_choice(dims, cin, cout, n, recon):
     """Each kernel of the weight gradient on both sides of where another takes over, against the oracle; the same
