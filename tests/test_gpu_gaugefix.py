@@ -135,3 +135,50 @@ def test_rotation_at_the_edges_of_its_launches(dims):
         assert orc.rel_l2(got, orc.d_eo(transform(U, Om), psi, BC)) < 1e-12
     g.close()
     ctx.close()
+
+
+def test_fixing_a_large_lattice_takes_no_device_memory():
+    """Past 64 MB of Omega the rotation is made in the links' own place: what the card has free is the same before
+    and after (a first field of the same size has loaded the kernels and what the runtime keeps for copies), Omega
+    is the product of the t-links and the float64 dslash that of the rotated ones (links constant over space, random
+    along t: Omega(t) is the same at every site of a slice, and the spatial links are rotated into another constant)."""
+    import torch
+    from paper_0810_5365_amd import wdirac as w
+    dims = (32, 32, 32, 16)   # 71 MB of Omega
+    X, Y, Z, T = dims
+    small = ls.gauge_field((2, 2, 2, T), 0.6, 80)[:, :, 0, 0, 0]   # (4, T, 3, 3)
+    U = np.ascontiguousarray(np.broadcast_to(small[:, :, None, None, None], (4, T, Z, Y, X, 3, 3)))
+    om = [np.eye(3, dtype=complex)]
+    for t in range(T - 1):
+        om.append(om[t] @ small[3, t])
+    om = np.stack(om)
+    Om = np.empty((T, Z, Y, X, 3, 3), dtype=np.complex128)
+    free = []
+    for _ in range(2):
+        ctx = w.Context(0)
+        g = w.Gauge(ctx, dims, BC, 18)
+        g.upload(U)
+        g.prepare(w.F64)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        w.wd_gauge_fix_temporal(g.handle, Om.ctypes.data)
+        free.append((before, torch.cuda.mem_get_info()[0]))
+        assert np.abs(Om - om[:, None, None, None]).max() < 1e-13
+        # a spinor constant over space, hopped onto the even sites: the same lattice two sites wide gives its values
+        col = ls.gaussian_complex((T, 4, 3), 81, ls.STREAM_SPINOR)
+        lat = w.lattice(dims, BC)
+        psi = np.broadcast_to(col[:, None, None, None], (T, Z, Y, X, 4, 3))
+        fin = w.pack(ctx, lat, w.ODD, w.F64, orc.eo_split(psi, dims, 1))
+        fo = w.new_field(lat, w.EVEN, w.F64)
+        w.wd_dslash(g.handle, w.EVEN, 0, w.F64, 1, fin.data_ptr(), fo.data_ptr())
+        got = w.unpack(ctx, lat, w.EVEN, w.F64, fo, (X * Y * Z * T // 2, 4, 3))
+        d2 = (2, 2, 2, T)
+        U2 = np.ascontiguousarray(np.broadcast_to(small[:, :, None, None, None], (4, T, 2, 2, 2, 3, 3)))
+        Om2 = np.ascontiguousarray(np.broadcast_to(om[:, None, None, None], (T, 2, 2, 2, 3, 3)))
+        psi2 = np.ascontiguousarray(np.broadcast_to(col[:, None, None, None], (T, 2, 2, 2, 4, 3)))
+        ref = orc.d_eo(transform(U2, Om2), orc.eo_split(psi2, d2, 1), BC).reshape(T, -1, 4, 3)
+        assert np.abs(ref - ref[:, :1]).max() < 1e-12      # constant over space, as it should be
+        assert np.abs(got.reshape(T, -1, 4, 3) - ref[:, :1]).max() < 1e-12
+        g.close()
+        ctx.close()
+    assert free[1][1] >= free[1][0]
