@@ -61,8 +61,8 @@ def kernel_source_sha():
     h = hashlib.sha256()
     csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_0810_5365_amd", "csrc")
     # everything that shapes the timed launches: the kernel body, its launcher, device helpers,
-    # the host core, the tuner that picks the launch shapes, and the step's composition
-    for f in ("dslash_body.h", "dslash.hip", "wd_device.h", "wd_core.h", "tune.hip", "api.hip"):
+    # the host core, the rule and the tuner that pick the launch shapes, and the step's composition
+    for f in ("dslash_body.h", "dslash.hip", "dslash_shape.h", "wd_device.h", "wd_core.h", "tune.hip", "api.hip"):
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()
 

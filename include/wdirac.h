@@ -426,7 +426,7 @@ int wd_tune_get_n(wd_context ctx, const char* key, int* out, int n);
  * WD_DSLASH_BLOCK, _REMAP, _NT, _PF, _RHS_INNER, _ZB  launch shape of an untuned dslash (all but
  *                          _NT ask for the kernel with one wave per 64 sites)
  * WD_DSLASH_SPLIT = 0 / 1  an untuned dslash with one / four waves per 64 sites (default: by size,
- *                          precision and number of rhs)
+ *                          precision, reals per link, number of rhs and launches of the call)
  * WD_DSLASH_MFMA = 0 / 1   16-bit multi-rhs dslash off / on the matrix cores, tuned or not
  * WD_BATCH_BLOCK, _WAVES, _PF  force the batch launch shape (tile width 64..256, waves per
  *                          compute unit, pipelined directions 0 / 1) instead of tuning it
